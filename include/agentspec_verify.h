@@ -189,11 +189,13 @@ int verify_attention_append(const verify_attn_params *params, int32_t total_q, i
  *            the others in class 1.  Class 0 in info[1..4], class 1 in
  *            info[6..9]: workgroups, query rows per row group, row groups
  *            per (request, KV head) at most, fixed units per workgroup (0:
- *            equal shares).  A unit is one 16-token block of one (request, KV
- *            head, row group) pair of the class's requests; units are
- *            numbered request by request, then KV head, then row group, then
- *            block, and workgroup w owns units [U w / N, U (w + 1) / N) of the
- *            class's U units (N = min(workgroups, U)).
+ *            equal shares; -1: whole pairs).  A unit is one 16-token block of
+ *            one (request, KV head, row group) pair of the class's requests;
+ *            units are numbered request by request, then KV head, then row
+ *            group, then block, and workgroup w owns units [U w / N,
+ *            U (w + 1) / N) of the class's U units (N = min(workgroups, U)).
+ *            With whole pairs workgroup w walks pair w = (request * Hkv + KV
+ *            head) * row groups + row group, all of its units.
  *   fp32:    info[1] splits per request at most, info[2] query rows per work
  *            item, info[3] row groups, info[4] KV blocks per split.
  * Same argument checks as verify_attention_workspace_size.

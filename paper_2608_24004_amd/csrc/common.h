@@ -138,6 +138,33 @@ __device__ __forceinline__ void dma16(uint32_t lds_wave_base, const void* src) {
                  : "memory", "m0");
 }
 
+// RUN consecutive KiB from global memory into LDS: load r moves bytes
+// [src + 1024 r + 16 l, + 16) to LDS byte lds + 1024 r + 16 l of lane l
+// (lane16 = 16 l).  src is wavefront-uniform; the immediate offset applies to
+// the global and to the LDS address.
+template <int RUN>
+__device__ __forceinline__ void dma16_run(uint32_t lds_wave_base, const void* src, uint32_t lane16) {
+    static_assert(RUN == 1 || RUN == 2 || RUN == 4, "13-bit immediate offsets");
+    const uint64_t u = (uint64_t)(uintptr_t)src;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    const void* const base = (const void*)(uintptr_t)(((uint64_t)hi << 32) | lo);
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_wave_base);
+    if constexpr (RUN == 4)
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:3072"
+                     : : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
+    else if constexpr (RUN == 2)
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:1024"
+                     : : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     : : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
+}
+
 // Wait until at most N vector-memory operations of this wavefront are in flight.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

@@ -17,6 +17,7 @@
 // t <= p, and with a sliding window W only t > p - W; the walk covers the
 // union of the rows' visible blocks only.
 #include <atomic>
+#include <type_traits>
 
 #include "common.h"
 
@@ -295,15 +296,29 @@ __global__ __launch_bounds__(kAttnThreads) void attn_valu(AttnArgs a) {
 // leaves one partial (normalised output + log-sum-exp) per workgroup in slot
 // P + w (P = pair index), and attn_combine_slots merges them.
 //
+// Launches of short pairs (whole_pairs) skip the schedule: workgroup w walks
+// pair w from end to end, and nothing is merged.
+//
 // Inside a workgroup the NW wavefronts split the pair's query rows (TPW tiles
 // of 16 rows each) and share the KV blocks: each block's K and V tiles (16
 // tokens x D, contiguous in the paged layout) are copied once, 16 bytes per
-// lane, straight from global memory into a ring of PD + 1 LDS stages (PD
-// blocks in flight), and read from there by every wavefront as MFMA operands.
-// The load stream runs straight across pair boundaries; the block id of each
-// block it loads is a scalar load issued one block earlier.
+// lane, straight from global memory into a ring of NS LDS stages, and read
+// from there by every wavefront as MFMA operands.  The load stream runs
+// straight across pair boundaries; the ids of the blocks it loads are scalar
+// loads issued one step earlier.
 //
-// Per block and 16-row tile, with lane = 16*lg + l16:
+// The walk goes in steps of two blocks (one where a pair or range ends).  What
+// bounds it: with one or two tiles per wavefront, HBM (1.2 GB of a decode
+// batch at 5.1 TB/s); with eight tiles per workgroup the chain of a step, its
+// LDS time and its scalar instructions.  Two blocks per step halve the
+// barriers, waits and maximum tests, double the products in flight, run PV at
+// the 32-key rate and make all LDS reads 16 bytes wide and conflict-free; the
+// steady-state loop keeps the scalar work of a step at address arithmetic.
+// Against one block per step: 43 GB of ragged long contexts 8.70 -> 7.60 ms
+// (long-row class 5.96 -> 4.97 ms), 4.6 GB at D = 64 with five tiles 893 ->
+// 850 us, a pair of 32 blocks alone on a compute unit 24 -> 14.7 us.
+//
+// Per 16-row tile, with lane = 16*lg + l16, for a single block:
 //   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = K (16 keys x 32 dims, lane
 //                 holds 8 consecutive dims of key l16: one 16-byte LDS read
 //                 of the x-packed K tile), B = Q^T (8 dims of row l16);
@@ -311,7 +326,8 @@ __global__ __launch_bounds__(kAttnThreads) void attn_valu(AttnArgs a) {
 //   O^T += V^T P^T v_mfma_f32_16x16x16_bf16, A = V^T (16 dims x 16 keys, lane
 //                 holds 4 keys of dim l16: one 8-byte read of the V^T tile),
 //                 B = P^T (the same 4 keys of row l16, straight from the S
-//                 registers after the online-softmax update).
+//                 registers after the online-softmax update);
+// two blocks permute the keys and take the 32-key PV product (see compute).
 // The output tile is O^T: lane holds dims 4lg..4lg+3 of row l16, so a row's
 // running max and rescale factor live in the lanes that own its scores.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -351,6 +367,7 @@ struct PArgs {
     int nwg;              // workgroups of the persistent launch
     int spb;              // > 0: fixed number of units per workgroup
     int inline_sched;     // 1: attn_persist computes the unit offsets itself
+    int whole;            // 1: workgroup w walks pair w from end to end; no schedule, no slots
     int rows_lo, rows_hi; // the launch's row class: requests whose group * n_i lies in
                           // [rows_lo, rows_hi]; the others belong to another launch
     const float* sinks;   // [Hq] sink logits (natural-log units) or null
@@ -390,12 +407,26 @@ __device__ __forceinline__ int64_t slot_o_index(int64_t slot, int rows_per_group
     return (slot * rows_per_group + (lr & ~15)) * D + ((d >> 4) * kWave + lane) * 4;
 }
 
+// p[k] by a scalar load: p and k are the same in every lane, and no kernel of
+// the launch writes the array (constant address space).  Left to itself the
+// compiler takes an index carried around a loop as divergent and loads into a
+// vector register, whose wait drains the whole prefetch ring.
+__device__ __forceinline__ int scalar_load(const int32_t* p, int64_t k) {
+    const uint64_t u = (uint64_t)(uintptr_t)(p + k);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    typedef const __attribute__((address_space(4))) int32_t* ConstPtr;
+    return *(ConstPtr)(uintptr_t)(((uint64_t)hi << 32) | lo);
+}
+
+// UNIFORM: i is the same in every lane (scalar loads).
+template <bool UNIFORM = false>
 __device__ __forceinline__ ReqGeom req_geom(const PArgs& a, const int32_t* __restrict__ q_start,
                                             const int32_t* __restrict__ seq_lens, int i) {
     ReqGeom r;
-    r.q0 = q_start[i];
-    r.n = q_start[i + 1] - r.q0;
-    int S = seq_lens[i];
+    r.q0 = UNIFORM ? scalar_load(q_start, i) : q_start[i];
+    r.n = (UNIFORM ? scalar_load(q_start, i + 1) : q_start[i + 1]) - r.q0;
+    int S = UNIFORM ? scalar_load(seq_lens, i) : seq_lens[i];
     S = max(0, min(S, min(a.max_seq_len, a.max_blocks * kBlockTokens)));
     r.S = S;
     const int key_lo = a.window > 0 ? max(0, S - r.n - a.window + 1) : 0;
@@ -411,12 +442,12 @@ __device__ __forceinline__ ReqGeom req_geom(const PArgs& a, const int32_t* __res
 // Rows past the launch's reach: a request with more than max_q_len rows can
 // need more row groups than the launch provides (rg_max); those rows are not
 // computed, and their outputs are written as a quiet NaN instead of being
-// left stale.  Threads t = t0, t0 + nt, ... cover the batch's requests.
+// left stale.  The calling thread covers requests i0, i0 + step, ... below i1.
 template <int D>
 __device__ void mark_unreached_rows(const PArgs& a, const int32_t* __restrict__ q_start,
-                                    uint16_t* __restrict__ out, int t0, int nt) {
+                                    uint16_t* __restrict__ out, int i0, int i1, int step) {
     const int reach = a.rg_max * a.rows_per_group;  // local rows of one (request, KV head)
-    for (int i = t0; i < a.num_seqs; i += nt) {
+    for (int i = i0; i < i1; i += step) {
         const int q0 = q_start[i];
         const int rows = a.group * (q_start[i + 1] - q0);
         if (rows < a.rows_lo || rows > a.rows_hi) continue;
@@ -444,7 +475,7 @@ __global__ __launch_bounds__(1024) void attn_schedule(PArgs a, const int32_t* __
                                                      const int32_t* __restrict__ seq_lens,
                                                      int32_t* __restrict__ unit_start,
                                                      uint16_t* __restrict__ out) {
-    mark_unreached_rows<D>(a, q_start, out, threadIdx.x, blockDim.x);
+    mark_unreached_rows<D>(a, q_start, out, threadIdx.x, a.num_seqs, blockDim.x);
     __shared__ int wsum[16];
     __shared__ int carry_s;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -489,19 +520,18 @@ struct Cursor {
     ReqGeom rq;
 };
 
-__device__ __forceinline__ void advance(const PArgs& a, const int32_t* __restrict__ q_start,
-                                        const int32_t* __restrict__ seq_lens, Cursor& c) {
-    if (++c.b < c.rq.b_lo + c.rq.nb) return;
-    c.b = c.rq.b_lo;
-    if (++c.r < c.rq.rg) return;
-    c.r = 0;
-    if (++c.g < a.hkv) return;
-    c.g = 0;
-    while (++c.i < a.num_seqs) {
-        c.rq = req_geom(a, q_start, seq_lens, c.i);
-        if (c.rq.rg > 0 && c.rq.nb > 0) break;
+// The pair after (i, g, r), whose request has geometry rq.
+__device__ __forceinline__ void next_pair(const PArgs& a, const int32_t* __restrict__ q_start,
+                                          const int32_t* __restrict__ seq_lens, int& i, int& g, int& r,
+                                          ReqGeom& rq) {
+    if (++r < rq.rg) return;
+    r = 0;
+    if (++g < a.hkv) return;
+    g = 0;
+    while (++i < a.num_seqs) {
+        rq = req_geom<true>(a, q_start, seq_lens, i);
+        if (rq.rg > 0 && rq.nb > 0) break;
     }
-    c.b = c.rq.b_lo;
 }
 
 // Batches of at most this many requests are scheduled inside attn_persist:
@@ -563,7 +593,7 @@ __device__ __forceinline__ Cursor locate_unit(const PArgs& a, const int32_t* __r
     }
     Cursor c;
     c.i = lo;
-    c.rq = req_geom(a, q_start, seq_lens, lo);
+    c.rq = req_geom<true>(a, q_start, seq_lens, lo);
     const int off = u - uniform_load(unit_start + lo);
     const int pq = off / c.rq.nb;  // pair within the request: head * rg + row group
     c.g = pq / c.rq.rg;
@@ -572,34 +602,37 @@ __device__ __forceinline__ Cursor locate_unit(const PArgs& a, const int32_t* __r
     return c;
 }
 
-// One online-softmax step of a 16-row tile over one 16-key block.  sacc holds
-// raw scores <q, k> in the MFMA result layout (lane 16 lg + l16: keys
-// key0 .. key0 + 3 of the tile's row l16, key0 = 16 b + 4 lg); row_j is the
+// One online-softmax step of a 16-row tile over NB consecutive 16-key blocks.
+// sacc holds raw scores <q, k> in the MFMA result layout (lane 16 lg + l16:
+// keys key0 .. key0 + 3 of each block for the tile's row l16, key0 = 16 b + 4 lg
+// in the first); row_j is the
 // row's draft position (-1: no row) and p_first the position of the request's
 // first row.  The exponentials are taken against the stored maximum m as long
 // as no score exceeds it by more than 2^kSlackLog2; only then (on a row's
 // first keys, and rarely after) does the wavefront reduce the new row maximum
 // over the row's four lanes and rescale l and o.  The weights stay below
 // 2^kSlackLog2, and bf16 rounds them with the same relative error at any
-// magnitude.  Returns the weights as the bf16 B operand of the PV product.
-template <int DT>
-__device__ __forceinline__ i16x4_t softmax_step(const f32x4_t& sacc, bool need_mask, int row_j,
-                                                int p_first, int key0, int window, float c,
-                                                float inv_c, float& m, float& l, float& thr,
-                                                float& neg_m, f32x4_t (&o)[DT]) {
-    float sv[4];
+// magnitude.  pw receives the weights as the bf16 B operand of the PV product,
+// two words per block.
+template <int NB, int DT>
+__device__ __forceinline__ void softmax_step(const f32x4_t (&sacc)[NB], bool need_mask, int row_j,
+                                             int p_first, const int (&key0)[NB], int window, float c,
+                                             float inv_c, float& m, float& l, float& thr, float& neg_m,
+                                             f32x4_t (&o)[DT], uint32_t (&pw)[2 * NB]) {
+    float sv[4 * NB];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sv[r] = sacc[r];
+    for (int r = 0; r < 4 * NB; ++r) sv[r] = sacc[r / 4][r % 4];
     if (need_mask) {
         const int p = p_first + row_j;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int key = key0 + r;
+        for (int r = 0; r < 4 * NB; ++r) {
+            const int key = key0[r / 4] + r % 4;
             const bool vis = row_j >= 0 && key <= p && (window == 0 || key > p - window);
             sv[r] = vis ? sv[r] : -INFINITY;
         }
     }
-    const float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+    float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+    if constexpr (NB == 2) mx = fmaxf(mx, fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
     if (__builtin_amdgcn_ballot_w64(!(mx <= thr))) {
         const float rmax = row_max_4lanes(mx) * c;
         if (rmax > m) {
@@ -615,11 +648,31 @@ __device__ __forceinline__ i16x4_t softmax_step(const f32x4_t& sacc, bool need_m
     }
     // exponent arguments are <= kSlackLog2: the raw v_exp_f32 is exact enough
     // and results below 2^-126 only flush to zero
-    float pr[4];
+    float pr[4 * NB];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c, neg_m));
-    l += (pr[0] + pr[1]) + (pr[2] + pr[3]);
-    return __builtin_bit_cast(i16x4_t, make_uint2(pack_bf16x2(pr[0], pr[1]), pack_bf16x2(pr[2], pr[3])));
+    for (int r = 0; r < 4 * NB; ++r) pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c, neg_m));
+#pragma unroll
+    for (int h = 0; h < NB; ++h) {
+        l += (pr[4 * h] + pr[4 * h + 1]) + (pr[4 * h + 2] + pr[4 * h + 3]);
+        pw[2 * h] = pack_bf16x2(pr[4 * h], pr[4 * h + 1]);
+        pw[2 * h + 1] = pack_bf16x2(pr[4 * h + 2], pr[4 * h + 3]);
+    }
+}
+
+// Wait until at most n blocks' loads (CPT per thread each, n <= MAXN) are in
+// flight.  n is wavefront-uniform; STEADY, its value in the steady state, is
+// tested first.
+template <int CPT, int STEADY, int MAXN>
+__device__ __forceinline__ void wait_blocks(int n) {
+    if constexpr (STEADY >= 0) {
+        if (n == STEADY) wait_vmcnt<CPT * STEADY>();
+        else wait_blocks<CPT, -1, MAXN>(n);
+    } else if constexpr (MAXN == 0) {
+        wait_vmcnt<0>();
+    } else {
+        if (n >= MAXN) wait_vmcnt<CPT * MAXN>();
+        else wait_blocks<CPT, -1, MAXN - 1>(n);
+    }
 }
 
 // Whether every row of the request sees every key of block b: the block lies
@@ -633,13 +686,14 @@ __device__ __forceinline__ bool block_needs_mask(int b, int p_first, int S, int 
 // Global->LDS loads need about sixteen wavefronts per compute unit to reach
 // full HBM bandwidth, so one-tile configurations are held to four waves per
 // SIMD (at most 128 registers each).
-// Waves per SIMD the persistent kernel is built for.  The fused append's
-// four-wavefront kernel is held to three, the residency of the plain one: its
-// patch would otherwise take it to 192 registers and two workgroups per
-// compute unit (long-context fused call 9.27 -> 8.66 ms); the few values it
-// then keeps in scratch are reloaded only on pair switches and patched blocks.
-template <int TPW, int NW = 1, bool APPEND = false>
-constexpr int persist_waves_per_eu() { return TPW == 1 ? 4 : (APPEND && NW == 4 && TPW == 2 ? 3 : 2); }
+// Waves per SIMD the persistent kernel is built for.  The four-wavefront
+// two-tile kernels are held to three (168 registers): three workgroups per
+// compute unit hide a step's chain of LDS reads, products and exponentials
+// better than two with deeper rings (long-row class of the 43 GB batch 4.97
+// against 5.06 ms).  The fused append's then keeps a few values in scratch,
+// reloaded only on pair switches and patched blocks.
+template <int TPW, int NW>
+constexpr int persist_waves_per_eu() { return TPW == 1 ? 4 : (NW == 4 && TPW == 2 ? 3 : 2); }
 
 // APPEND: the fused KV append (verify_attention_append).  The request's new
 // tokens, positions S_i - n_i .. S_i - 1 of rows q_start[i] .. q_start[i+1]-1,
@@ -648,9 +702,9 @@ constexpr int persist_waves_per_eu() { return TPW == 1 ? 4 : (APPEND && NW == 4 
 // those blocks only), and the workgroup of the pair's first row group also
 // stores them into the cache.  Readers never depend on that store, so no
 // ordering between workgroups is needed.
-template <int D, int NW, int TPW, int PD, bool APPEND>
+template <int D, int NW, int TPW, int NS, bool APPEND>
 __global__ __launch_bounds__(NW * kWave)
-__attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) void attn_persist(
+__attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_persist(
     PArgs a, const uint16_t* __restrict__ qg, const uint8_t* __restrict__ kcg,
     const uint8_t* __restrict__ vcg, const int32_t* __restrict__ block_tables,
     const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_start,
@@ -664,67 +718,101 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
     constexpr int KC = D / 32;                        // QK^T steps of 32 dims
     constexpr int DT = D / 16;                        // PV output tiles of 16 dims
     constexpr int ROWS = NW * TPW * 16;
-    constexpr int NS = PD + 1;                        // LDS stages: PD blocks in flight
+    constexpr int STEP = 2;                           // blocks per step at most
     static_assert(CH % NT == 0, "every thread loads the same number of chunks");
-    static_assert(CPT * (NS - 2) < 64, "vmcnt range");
+    static_assert(NS >= 4 && NS <= 32 && CPT * (NS - 1) < 64, "ok_mask bits and vmcnt range");
+    static_assert(2 * TILE_BYTES >= (int)sizeof(int32_t) * (kInlineSchedSeqs + 1), "schedule scan in a stage");
 
     __shared__ __attribute__((aligned(16))) uint8_t stage[NS][2 * TILE_BYTES];
-    __shared__ int32_t sched[kInlineSchedSeqs + 1];
+    // the schedule scan lives in the last stage, which is first loaded after
+    // the first step's barrier
+    int32_t* const sched = reinterpret_cast<int32_t*>(stage[NS - 1]);
 
     const int w = blockIdx.x;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
-    const int wv = tid / kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);  // wavefront-uniform
     const int l16 = lane & 15, lg = lane >> 4;
 
-    const int32_t* ustart = unit_start;
-    if (a.inline_sched) {
-        if (wv == 0) {
-            sched_prefix(a, q_start, seq_lens, sched, lane);
-            if (w == 0) {
-                for (int i = lane; i <= a.num_seqs; i += kWave) unit_start[i] = sched[i];
-                mark_unreached_rows<D>(a, q_start, out, lane, kWave);
-            }
-        }
-        __syncthreads();
-        ustart = sched;
-    }
-    const int U = uniform_load(ustart + a.num_seqs);
     int us, ue;
-    unit_range(a, U, w, us, ue);
-    if (us >= ue) return;
-    const Cursor c0 = locate_unit(a, q_start, seq_lens, ustart, us);
+    Cursor c0;
+    if (a.whole) {
+        // one pair per workgroup, unit u of it is block b_lo + u
+        const int per_req = a.hkv * a.rg_max;
+        c0.i = w / per_req;
+        c0.g = (w - c0.i * per_req) / a.rg_max;
+        c0.r = w - c0.i * per_req - c0.g * a.rg_max;
+        c0.rq = req_geom<true>(a, q_start, seq_lens, c0.i);
+        c0.b = c0.rq.b_lo;
+        if (c0.g == 0 && c0.r == 0 && tid == 0)
+            mark_unreached_rows<D>(a, q_start, out, c0.i, c0.i + 1, 1);
+        if (c0.r >= c0.rq.rg) return;
+        us = 0;
+        ue = c0.rq.nb;
+        if (ue == 0) {  // no key: zeros for the pair's rows
+            const int r1 = min(ROWS, a.group * c0.rq.n - c0.r * ROWS);
+            for (int e = tid; e < r1 * (D / 4); e += NT) {
+                const int rr = c0.r * ROWS + e / (D / 4);
+                const int64_t hrow =
+                    (int64_t)(c0.rq.q0 + rr / a.group) * a.hq + c0.g * a.group + rr % a.group;
+                *reinterpret_cast<uint2*>(out + hrow * D + e % (D / 4) * 4) = make_uint2(0, 0);
+            }
+            return;
+        }
+    } else {
+        const int32_t* ustart = unit_start;
+        if (a.inline_sched) {
+            if (wv == 0) {
+                sched_prefix(a, q_start, seq_lens, sched, lane);
+                if (w == 0) {
+                    for (int i = lane; i <= a.num_seqs; i += kWave) unit_start[i] = sched[i];
+                    mark_unreached_rows<D>(a, q_start, out, lane, a.num_seqs, kWave);
+                }
+            }
+            __syncthreads();
+            ustart = sched;
+        }
+        const int U = uniform_load(ustart + a.num_seqs);
+        unit_range(a, U, w, us, ue);
+        if (us >= ue) return;
+        c0 = locate_unit(a, q_start, seq_lens, ustart, us);
+    }
 
     const uint32_t stage_lds =
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&stage[0][0];
     // One unit = one block's K and V tiles, copied into an LDS stage with CPT
-    // global->LDS loads per thread (wavefront w's c-th load fills the 1 KiB
-    // at chunk c*NT + 64w).  Every call issues exactly CPT loads, invalid
-    // block ids reading block 0 (compute skips them through ok_mask), so the
-    // explicit vmcnt waits below count exactly.
+    // global->LDS loads of 1 KiB per wavefront: wavefront w copies chunks
+    // [w CPT, (w + 1) CPT) of the 2 TILE_BYTES / 1 KiB (K's first).  A
+    // wavefront's loads from one tile share m0, the scalar base address and
+    // the lane offset; the instruction's immediate offset, which the hardware
+    // adds to both the global and the LDS address, steps through them.  Every
+    // call issues exactly CPT loads, invalid block ids reading block 0
+    // (compute skips them through ok_mask), so the explicit vmcnt waits below
+    // count exactly.
     // Bit s: stage s holds a valid block.  Every wavefront runs the same
     // loader steps, so each keeps its own copy in a scalar register.
     uint32_t ok_mask = 0;
-    auto dma_unit = [&](const Cursor& c, int st, int phys) {
-        const int g = c.g;
+    const uint32_t lane16 = (uint32_t)lane * 16;
+    constexpr int TILE_LOADS = TILE_BYTES / 1024;         // loads of one tile
+    constexpr int RUN = CPT < TILE_LOADS ? CPT : TILE_LOADS;  // of them by one wavefront
+    auto dma_unit = [&](int g, int st, int phys) {
         const bool ok = phys >= 0 && phys < a.num_blocks;
         ok_mask = ok ? (ok_mask | (1u << st)) : (ok_mask & ~(1u << st));
         phys = ok ? phys : 0;
         const int64_t off = ((int64_t)phys * a.hkv + g) * TILE_BYTES;
         const uint32_t base = stage_lds + st * (2 * TILE_BYTES);
 #pragma unroll
-        for (int c2 = 0; c2 < CPT; ++c2) {
-            const int wchunk = c2 * NT + wv * kWave;  // first chunk of this wavefront's load
-            const int idx = wchunk + lane;
-            const uint8_t* srcp = idx < CH / 2 ? kcg + off + idx * 16 : vcg + off + (idx - CH / 2) * 16;
-            dma16(base + wchunk * 16, srcp);
+        for (int c = 0; c < CPT; c += RUN) {
+            const int first = wv * CPT + c;  // this run's first load of the block's 2 TILE_LOADS
+            const uint8_t* src = first < TILE_LOADS ? kcg + off + first * 1024
+                                                    : vcg + off + (first - TILE_LOADS) * 1024;
+            dma16_run<RUN>(base + first * 1024, src, lane16);
         }
     };
 
-    // ---- state of the pair being computed
-    int st_i = -1, st_g = -1, st_rg = -1;
+    // ---- state of the pair being computed: the pair cc points into
+    Cursor cc = c0;
     int st_ps = 0;  // first unit of the pair
-    ReqGeom srq{};
     bool active = false;
     bf16x8_t qop[TPW][KC];
     int row_j[TPW];
@@ -739,21 +827,17 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
     // reaches) and the position of its first row, S_i - n_i
     int st_nlo = 0, st_nhi = 0, st_p0 = 0;
 
-    // Pair of cursor c, reached at unit u.
-    auto init_pair = [&](const Cursor& c, int u) {
-        st_i = c.i;
-        st_ps = u - (c.b - c.rq.b_lo);
-        srq = c.rq;
-        st_g = c.g;
-        st_rg = c.r;
+    // The pair of cc, reached at unit u.
+    auto init_pair = [&](int u) {
+        st_ps = u - (cc.b - cc.rq.b_lo);
         if constexpr (APPEND) {
-            const int s_raw = uniform_load(seq_lens + c.i);
-            st_p0 = s_raw - srq.n;
+            const int s_raw = scalar_load(seq_lens, cc.i);
+            st_p0 = s_raw - cc.rq.n;
             st_nlo = max(st_p0, 0);
-            st_nhi = min(s_raw, srq.S);
+            st_nhi = min(s_raw, cc.rq.S);
         }
-        const int rows = a.group * srq.n;
-        const int wrow0 = st_rg * ROWS + wv * TPW * 16;
+        const int rows = a.group * cc.rq.n;
+        const int wrow0 = cc.r * ROWS + wv * TPW * 16;
         active = wrow0 < rows;
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
@@ -761,7 +845,7 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
             const bool valid = rr < rows;
             const int j = rr / a.group, gh = rr - j * a.group;
             row_j[t] = valid ? j : -1;
-            const int64_t base = ((int64_t)(srq.q0 + j) * a.hq + st_g * a.group + gh) * D;
+            const int64_t base = ((int64_t)(cc.rq.q0 + j) * a.hq + cc.g * a.group + gh) * D;
 #pragma unroll
             for (int cc = 0; cc < KC; ++cc) {
                 uint4 v = make_uint4(0, 0, 0, 0);
@@ -772,7 +856,7 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
             l_r[t] = 0.f;
             thr[t] = -INFINITY;
             neg_m[t] = 0.f;
-            sink_l2[t] = a.sinks && valid ? a.sinks[st_g * a.group + gh] * kLog2e : -INFINITY;
+            sink_l2[t] = a.sinks && valid ? a.sinks[cc.g * a.group + gh] * kLog2e : -INFINITY;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) o[t][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         }
@@ -785,22 +869,22 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
 
     auto flush_pair = [&]() {
         if (!active) return;
-        const bool whole = st_ps >= us && st_ps + srq.nb <= ue;
-        const int rows = a.group * srq.n;
-        const int64_t slot = (int64_t)(st_i * a.hkv + st_g) * a.rg_max + st_rg + w;
+        const bool whole = st_ps >= us && st_ps + cc.rq.nb <= ue;
+        const int rows = a.group * cc.rq.n;
+        const int64_t slot = (int64_t)(cc.i * a.hkv + cc.g) * a.rg_max + cc.r + w;
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
             float L = l_r[t];
             L += __shfl_xor(L, 16);
             L += __shfl_xor(L, 32);
             const int lr = (wv * TPW + t) * 16 + l16;
-            const int rr = st_rg * ROWS + lr;
+            const int rr = cc.r * ROWS + lr;
             if (rr >= rows) continue;
             if (whole) {
                 const float den = L + (a.sinks ? exp2f(sink_l2[t] - m_r[t]) : 0.f);
                 const float inv = den > 0.f ? 1.f / den : 0.f;
                 const int j = rr / a.group, gh = rr - j * a.group;
-                const int64_t hrow = (int64_t)(srq.q0 + j) * a.hq + st_g * a.group + gh;
+                const int64_t hrow = (int64_t)(cc.rq.q0 + j) * a.hq + cc.g * a.group + gh;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
                     const int d0 = dt * 16 + 4 * lg;
@@ -824,37 +908,96 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
         }
     };
 
-    auto compute = [&](int st, int b) {
-        if (!active || !((ok_mask >> st) & 1u)) return;
-        const uint8_t* ks = stage[st];
-        const uint8_t* vs = stage[st] + TILE_BYTES;
-        f32x4_t sacc[TPW];
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) sacc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int cc = 0; cc < KC; ++cc) {
-            const bf16x8_t kop =
-                as_bf16x8(*reinterpret_cast<const uint4*>(ks + ((cc * 4 + lg) * 16 + l16) * 16));
-#pragma unroll
-            for (int t = 0; t < TPW; ++t)
-                sacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop, qop[t][cc], sacc[t], 0, 0, 0);
+    // One step of the walk: block b in stage st, and with NB = 2 block b + 1
+    // in stage st2.
+    //
+    // Two blocks are one 32-key step.  The PV product then takes 32 keys per
+    // MFMA, and the key order is chosen so that every LDS read is 16 bytes
+    // wide and free of bank conflicts: row m of the two QK products stands for
+    // the keys below (t within the block), so that lane group lg ends up with
+    // eight consecutive keys of one block, the 16 bytes of a V^T row that it
+    // reads as its share of the PV operand.
+    //     m        0-3     4-7      8-11    12-15
+    //     first    A 0-3   A 8-11   B 4-7   B 12-15
+    //     second   A 4-7   A 12-15  B 0-3   B 8-11
+    // (Single blocks read V^T by 8 bytes, with two-way conflicts: the two
+    // 8-byte halves of a row lie in the same bank group as those of the row
+    // eight further on.)
+    auto compute = [&](auto nb, bool masked, int st, int st2, int b) {
+        constexpr int NB = decltype(nb)::value;
+        const bool b_row = NB == 2 && l16 >= 8, b_lane = NB == 2 && lg >= 2;
+        const uint8_t* const kb = stage[b_row ? st2 : st] + lg * 256;
+        const uint8_t* const vb = stage[b_lane ? st2 : st] + TILE_BYTES;
+        int kt[NB];  // byte offset of this lane's key in each QK product
+        if constexpr (NB == 2) {
+            kt[0] = (((l16 >> 2) & 1) * 8 + (l16 >> 3) * 4 + (l16 & 3)) * 16;
+            kt[1] = kt[0] ^ 64;
+        } else {
+            kt[0] = l16 * 16;
         }
-        const int p_first = srq.S - srq.n;  // position of the request's first query row
-        const bool need_mask = block_needs_mask(b, p_first, srq.S, a.window);
-        i16x4_t pop[TPW];
+        f32x4_t sacc[TPW][NB];
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
-            pop[t] = softmax_step<DT>(sacc[t], need_mask, row_j[t], p_first, b * kBlockTokens + 4 * lg,
-                                      a.window, a.scale_log2, a.inv_scale_log2, m_r[t], l_r[t],
-                                      thr[t], neg_m[t], o[t]);
+#pragma unroll
+            for (int h = 0; h < NB; ++h) sacc[t][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int cc4 = 0; cc4 < KC; ++cc4) {
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+                const bf16x8_t kop = as_bf16x8(*reinterpret_cast<const uint4*>(kb + kt[h] + cc4 * 1024));
+#pragma unroll
+                for (int t = 0; t < TPW; ++t)
+                    sacc[t][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop, qop[t][cc4], sacc[t][h], 0, 0, 0);
+            }
+        }
+        const int p_first = cc.rq.S - cc.rq.n;  // position of the request's first query row
+        int key0[NB];
+        if constexpr (NB == 2) {
+            const int k8 = (b + b_lane) * kBlockTokens + (lg & 1) * 8;
+            key0[0] = k8 + (b_lane ? 4 : 0);
+            key0[1] = k8 + (b_lane ? 0 : 4);
+        } else {
+            key0[0] = b * kBlockTokens + 4 * lg;
+        }
+        uint32_t pw[TPW][2 * NB];
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            softmax_step<NB, DT>(sacc[t], masked, row_j[t], p_first, key0, a.window, a.scale_log2,
+                                 a.inv_scale_log2, m_r[t], l_r[t], thr[t], neg_m[t], o[t], pw[t]);
+            if constexpr (NB == 2) {  // ascending keys
+                const uint32_t w0 = pw[t][0], w1 = pw[t][1];
+                pw[t][0] = b_lane ? pw[t][2] : w0;
+                pw[t][1] = b_lane ? pw[t][3] : w1;
+                pw[t][2] = b_lane ? w0 : pw[t][2];
+                pw[t][3] = b_lane ? w1 : pw[t][3];
+            }
+        }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
-            const uint2 vv = *reinterpret_cast<const uint2*>(vs + (dt * 16 + l16) * 32 + lg * 8);
-            const i16x4_t vop = __builtin_bit_cast(i16x4_t, vv);
+            if constexpr (NB == 2) {
+                const bf16x8_t vop = as_bf16x8(
+                    *reinterpret_cast<const uint4*>(vb + (dt * 16 + l16) * 32 + (lg & 1) * 16));
 #pragma unroll
-            for (int t = 0; t < TPW; ++t)
-                o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vop, pop[t], o[t][dt], 0, 0, 0);
+                for (int t = 0; t < TPW; ++t)
+                    o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        vop, as_bf16x8(make_uint4(pw[t][0], pw[t][1], pw[t][2], pw[t][3])), o[t][dt], 0, 0, 0);
+            } else {
+                const i16x4_t vop = __builtin_bit_cast(
+                    i16x4_t, *reinterpret_cast<const uint2*>(vb + (dt * 16 + l16) * 32 + lg * 8));
+#pragma unroll
+                for (int t = 0; t < TPW; ++t)
+                    o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                        vop, __builtin_bit_cast(i16x4_t, make_uint2(pw[t][0], pw[t][1])), o[t][dt], 0, 0, 0);
+            }
         }
+    };
+    // The blocks of a step whose ids are valid.
+    auto compute_step = [&](bool masked, int st, int st2, bool two, int b) {
+        const bool ok1 = (ok_mask >> st) & 1u, ok2 = two && ((ok_mask >> st2) & 1u);
+        // two plain ifs: with an else the compiler keeps the accumulators twice
+        const bool both = ok1 && ok2 && active, one = (ok1 || ok2) && !both && active;
+        if (both) compute(std::integral_constant<int, 2>{}, masked, st, st2, b);
+        if (one) compute(std::integral_constant<int, 1>{}, masked, ok1 ? st : st2, 0, ok1 ? b : b + 1);
     };
 
     // APPEND: overwrite the new tokens of block b in stage st with their K and
@@ -866,16 +1009,16 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
         const int t_lo = max(st_nlo - pos0, 0), t_hi = min(st_nhi - pos0, kBlockTokens);
         uint8_t* ks = stage[st];
         uint16_t* vs = reinterpret_cast<uint16_t*>(stage[st] + TILE_BYTES);
-        const bool writer = st_rg == 0;
-        const int phys = uniform_load(block_tables + (int64_t)st_i * a.max_blocks + b);
-        const int64_t toff = ((int64_t)phys * a.hkv + st_g) * TILE_BYTES;
+        const bool writer = cc.r == 0;
+        const int phys = scalar_load(block_tables, (int64_t)cc.i * a.max_blocks + b);
+        const int64_t toff = ((int64_t)phys * a.hkv + cc.g) * TILE_BYTES;
         uint8_t* kw = const_cast<uint8_t*>(kcg) + toff;
         uint16_t* vw = reinterpret_cast<uint16_t*>(const_cast<uint8_t*>(vcg) + toff);
         // K and V of one token's 8 dims per step, both loads in flight together
         for (int e = tid; e < (t_hi - t_lo) * DC; e += NT) {
             const int t = t_lo + e / DC, dc = e % DC;
-            const int64_t row = srq.q0 + (pos0 + t - st_p0);
-            const int64_t src = (row * a.hkv + st_g) * D + dc * 8;
+            const int64_t row = cc.rq.q0 + (pos0 + t - st_p0);
+            const int64_t src = (row * a.hkv + cc.g) * D + dc * 8;
             const uint4 kv = ld16(k_new + src);
             const uint4 vv = ld16(v_new + src);
             const int kchunk = dc * kBlockTokens + t;
@@ -893,75 +1036,172 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW, APPEND>()))) vo
         }
     };
 
-    // ---- pipeline: a ring of NS = PD + 1 LDS stages, PD blocks in flight.
-    // At unit uu: wait for this thread's loads of uu (the PD - 1 younger units
-    // may stay in flight), barrier (everyone's loads of uu have landed and
-    // everyone is done with uu - 1), refill the stage of uu - 1 with unit
-    // uu + PD, compute uu.  The loader cursor stops at the last unit and loads
-    // it again instead of issuing nothing, keeping the count fixed.
-    Cursor lc = c0;
-    int lu = us;
-    // Block id of the loader's unit: a scalar load, issued once the previous
-    // unit's compute has read its LDS operands (so that no LDS wait there
-    // also waits for it) and consumed after the next barrier.
-    auto fetch_phys = [&]() { return block_tables[(int64_t)lc.i * a.max_blocks + lc.b]; };
-    auto dma_next = [&](int st, int phys) {
-        dma_unit(lc, st, phys);
-        if (lu + 1 < ue) {
-            advance(a, q_start, seq_lens, lc);
-            ++lu;
+    // ---- pipeline: a ring of NS LDS stages, one block each, in walk order.  A
+    // step computes the next two blocks, or one where the pair or the range
+    // ends after it: wait for this thread's loads of the step's blocks (younger
+    // ones may stay in flight), barrier (everyone's loads of them have landed
+    // and everyone is done with the blocks before), refill the stages of the
+    // previous step, compute.  `issued` and `done` count blocks from us.
+    const int total = ue - us;
+    int issued = 0, done = 0;
+    // The loader's next two blocks (head, block id): `fetched` blocks have been
+    // looked up, the l_ values are the cursor of the next, whose request's table
+    // row starts at lrow.  The ids are scalar loads, issued once a step's
+    // compute has read its LDS operands (so that no LDS wait there also waits
+    // for them) and consumed after the next barrier.
+    int l_i = c0.i, l_g = c0.g, l_rg = c0.r, l_b = c0.b, l_end = c0.rq.b_lo + c0.rq.nb;
+    const int32_t* lrow = block_tables + (int64_t)l_i * a.max_blocks;
+    int fetched = 0, g0 = 0, g1 = 0, phys0 = 0, phys1 = 0;
+    auto fetch_to = [&](int want) {  // look up blocks until `want` are (at most two ahead)
+        if (fetched + 2 == want && l_b + 2 < l_end) {
+            g0 = g1 = l_g;
+            phys0 = scalar_load(lrow, l_b);
+            phys1 = scalar_load(lrow, l_b + 1);
+            l_b += 2;
+            fetched = want;
+            return;
         }
-    };
-#pragma unroll
-    for (int r = 0; r < PD; ++r) dma_next(r, fetch_phys());
-    int phys_next = fetch_phys();
-
-    Cursor cc = c0;
-    init_pair(cc, us);
-    int st = 0;
-    for (int uu = us; uu < ue; ++uu) {
-        wait_vmcnt<CPT * (PD - 1)>();
-        lds_barrier();
-        dma_next(st == 0 ? NS - 1 : st - 1, phys_next);
-        if (cc.i != st_i || cc.g != st_g || cc.r != st_rg) {
-            flush_pair();
-            init_pair(cc, uu);
-        }
-        if constexpr (APPEND) {
-            // block-uniform: every wavefront takes the same branch
-            const int pos0 = cc.b * kBlockTokens;
-            if (((ok_mask >> st) & 1u) && pos0 < st_nhi && pos0 + kBlockTokens > st_nlo) {
-                patch_new(st, cc.b);
-                lds_barrier();
+#pragma unroll 1
+        while (fetched < want) {
+            g0 = g1;
+            phys0 = phys1;
+            g1 = l_g;
+            phys1 = scalar_load(lrow, l_b);
+            ++fetched;
+            if (++l_b == l_end && fetched < total) {
+                ReqGeom rq = req_geom<true>(a, q_start, seq_lens, l_i);  // rather than kept
+                next_pair(a, q_start, seq_lens, l_i, l_g, l_rg, rq);
+                l_b = rq.b_lo;
+                l_end = rq.b_lo + rq.nb;
+                lrow = block_tables + (int64_t)l_i * a.max_blocks;
             }
         }
-        compute(st, cc.b);
-        asm volatile("" ::: "memory");
-        phys_next = fetch_phys();
-        advance(a, q_start, seq_lens, cc);
-        st = st == NS - 1 ? 0 : st + 1;
+        if (want == total && fetched == issued + 1) {  // the last block
+            g0 = g1;
+            phys0 = phys1;
+        }
+    };
+    int st_next = 0;  // stage of the next block to load
+    auto issue_to = [&](int want) {  // load blocks until `want` are (at most two)
+#pragma unroll 1
+        while (issued < want) {
+            dma_unit(g0, st_next, phys0);
+            st_next = st_next == NS - 1 ? 0 : st_next + 1;
+            g0 = g1;
+            phys0 = phys1;
+            ++issued;
+        }
+    };
+#pragma unroll 1
+    while (issued < min(NS - 1, total)) {
+        fetch_to(min(issued + 2, total));
+        issue_to(min(min(issued + 2, NS - 1), total));
     }
-    // no global->LDS load may still be writing when the workgroup's LDS is freed
-    wait_vmcnt<0>();
-    flush_pair();
+    fetch_to(min(issued + 2, total));
+
+    int st = 0;
+    bool fresh = true;
+    for (;;) {
+        if (fresh) init_pair(us + done);
+        fresh = false;
+        const int p_first = cc.rq.S - cc.rq.n;
+        // Steady state: steps whose blocks every row sees in full, with as
+        // many blocks to load, and no pair end for the walk or the loader.
+        // Nothing is left to decide in them but the ids' validity: the scalar
+        // work per block, which all wavefronts repeat, was as long as the
+        // products' (94 scalar against 98 vector instructions per block).
+        {
+            int lim = min(cc.rq.b_lo + cc.rq.nb, (p_first + 1) >> 4) - cc.b;
+            if constexpr (APPEND) lim = min(lim, (st_nlo >> 4) - cc.b);
+            lim = min(min(lim, total - fetched), l_end - 1 - l_b);
+            if (a.window > 0 && cc.b * kBlockTokens < cc.rq.S - a.window) lim = 0;
+            if (issued - done != NS - STEP || g0 != l_g || g1 != l_g) lim = 0;
+            const int steps = __builtin_amdgcn_readfirstlane(lim >= STEP ? lim / STEP : 0);
+            if (steps > 0) {
+                const int32_t* ids = lrow + l_b;
+#pragma unroll 1
+                for (int k = 0; k < steps; ++k) {
+                    wait_vmcnt<CPT * (NS - 2 * STEP)>();
+                    lds_barrier();
+                    dma_unit(l_g, st_next, phys0);
+                    st_next = st_next == NS - 1 ? 0 : st_next + 1;
+                    dma_unit(l_g, st_next, phys1);
+                    st_next = st_next == NS - 1 ? 0 : st_next + 1;
+                    const int st2 = st == NS - 1 ? 0 : st + 1;
+                    compute_step(false, st, st2, true, cc.b);
+                    asm volatile("" ::: "memory");
+                    phys0 = scalar_load(ids, 0);
+                    phys1 = scalar_load(ids, 1);
+                    ids += STEP;
+                    st = st2 == NS - 1 ? 0 : st2 + 1;
+                }
+                issued += steps * STEP;
+                done += steps * STEP;
+                fetched += steps * STEP;
+                l_b += steps * STEP;
+                cc.b += steps * STEP;
+            }
+        }
+        const int left = cc.rq.b_lo + cc.rq.nb - cc.b;  // blocks of the pair from here
+        if (left > 0 && done < total) {
+            const bool two = left > 1 && done + 1 < total;
+            const int cnt = two ? 2 : 1;
+            const int st2 = st == NS - 1 ? 0 : st + 1;
+            wait_blocks<CPT, NS - 2 * STEP, NS - 2>(issued - done - cnt);
+            lds_barrier();
+            issue_to(min(done + NS, total));
+            if constexpr (APPEND) {
+                // block-uniform: every wavefront takes the same branches
+                const int pos0 = cc.b * kBlockTokens;
+                if (pos0 < st_nhi && pos0 + cnt * kBlockTokens > st_nlo) {
+#pragma unroll 1
+                    for (int h = 0; h < cnt; ++h) {
+                        const int pos = pos0 + h * kBlockTokens, sth = h ? st2 : st;
+                        if (((ok_mask >> sth) & 1u) && pos < st_nhi && pos + kBlockTokens > st_nlo)
+                            patch_new(sth, cc.b + h);
+                    }
+                    lds_barrier();
+                }
+            }
+            const bool masked = block_needs_mask(cc.b, p_first, cc.rq.S, a.window) ||
+                                (two && block_needs_mask(cc.b + 1, p_first, cc.rq.S, a.window));
+            compute_step(masked, st, st2, two, cc.b);
+            asm volatile("" ::: "memory");
+            fetch_to(min(issued + 2, total));
+            done += cnt;
+            cc.b += cnt;
+            st = two ? (st2 == NS - 1 ? 0 : st2 + 1) : st2;
+            if (left > cnt && done < total) continue;
+        }
+        flush_pair();
+        if (done >= total) return;
+        next_pair(a, q_start, seq_lens, cc.i, cc.g, cc.r, cc.rq);
+        cc.b = cc.rq.b_lo;
+        fresh = true;
+    }
 }
 
 // Merges the partial slots of pairs cut by workgroup range boundaries, and
 // writes the zero output of rows whose request has no key.  Grid (pairs, row
 // chunks); a thread owns one row and four consecutive output dimensions.  The
 // slots of a row are read kCombineSlots at a time, every load of a round
-// issued before any is used (a pair is cut into a handful of slots, so one
-// round usually covers it), and merged with a running maximum.
+// issued before any is used, and merged with a running maximum.  In a full
+// batch a pair is cut into a handful of slots and one round covers it.  Where
+// few pairs are cut into many (SG = 4), four thread groups share a row: each
+// takes every fourth round, and their sums are merged through LDS (24 slots:
+// three rounds of latency -> one; one request of 95 blocks, whole call 16.3 ->
+// 13.1 us).
 constexpr int kCombineThreads = 256;
 constexpr int kCombineSlots = 8;
 
-template <int D>
-__global__ __launch_bounds__(kCombineThreads) void attn_combine_slots(
+template <int D, int SG>
+__global__ __launch_bounds__(kCombineThreads) __attribute__((amdgpu_waves_per_eu(8)))
+void attn_combine_slots(
     PArgs a, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_start,
     const int32_t* __restrict__ unit_start, const uint16_t* __restrict__ slot_o,
     const float* __restrict__ slot_lse, uint16_t* __restrict__ out) {
     constexpr int QUADS = D / 4;                       // 4-dim vectors per row
-    constexpr int RPB = kCombineThreads / QUADS;       // rows per workgroup
+    constexpr int RPB = kCombineThreads / QUADS / SG;  // rows per workgroup
     const int P = blockIdx.x;
     const int per_req = a.hkv * a.rg_max;
     const int i = P / per_req;
@@ -974,10 +1214,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_slots(
     const ReqGeom rq = req_geom(a, q_start, seq_lens, i);
     if (rg >= rq.rg) return;
     const int ROWS = a.rows_per_group;
-    const int rows = a.group * rq.n;
-    const int lr = blockIdx.y * RPB + threadIdx.x / QUADS;  // row within the group
-    const int rr = rg * ROWS + lr;
-    if (lr >= ROWS || rr >= rows) return;
+    const int group_rows = min(ROWS, a.group * rq.n - rg * ROWS);  // rows of this row group
     const bool empty = rq.nb == 0;
     int wf = 0, wl = 0;
     if (!empty) {
@@ -986,60 +1223,97 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_slots(
         wl = owner_of(a, ps + rq.nb - 1, U);
         if (wf == wl) return;  // finished in place by its only workgroup
     }
-    const int d0 = (threadIdx.x % QUADS) * 4;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    if (!empty) {
-        // slots of the pair: one per workgroup wf .. wl; a slot holding
-        // log-sum-exp -inf (no visible key in its range) adds nothing
-        const int64_t slot0 = (int64_t)P + wf;
-        const int ns = wl - wf + 1;
+    const int item = threadIdx.x % (kCombineThreads / SG);   // (row, quad) of the workgroup
+    const int sg = threadIdx.x / (kCombineThreads / SG);     // slot group
+    const int d0 = (item % QUADS) * 4;
+    // one pass, unless the request has more rows than the launch was sized for
+    for (int base = blockIdx.y * RPB; base < group_rows; base += gridDim.y * RPB) {
+        const int lr = base + item / QUADS;  // row within the group
+        const int rr = rg * ROWS + lr;
+        const bool in_row = lr < group_rows;
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
         float M = -INFINITY, L = 0.f;
-        for (int s0 = 0; s0 < ns; s0 += kCombineSlots) {
-            float lse[kCombineSlots];
-            f32x4_t o[kCombineSlots];
-            // every load is issued unconditionally (slots past the pair's last
-            // re-read the last one and are masked afterwards), so that the
-            // round's loads leave back to back; conditional loads compiled to a
-            // branch and a wait per slot, one memory latency each
-            uint2 v[kCombineSlots];
+        if (!empty && in_row) {
+            // slots of the pair: one per workgroup wf .. wl; a slot holding
+            // log-sum-exp -inf (no visible key in its range) adds nothing
+            const int64_t slot0 = (int64_t)P + wf;
+            const int ns = wl - wf + 1;
+            for (int s0 = sg * kCombineSlots; s0 < ns; s0 += SG * kCombineSlots) {
+                float lse[kCombineSlots];
+                f32x4_t o[kCombineSlots];
+                // every load is issued unconditionally (slots past the pair's last
+                // re-read the last one and are masked afterwards), so that the
+                // round's loads leave back to back; conditional loads compiled to a
+                // branch and a wait per slot, one memory latency each
+                uint2 v[kCombineSlots];
 #pragma unroll
-            for (int k = 0; k < kCombineSlots; ++k) {
-                const int64_t sl = slot0 + min(s0 + k, ns - 1);
-                lse[k] = slot_lse[sl * ROWS + lr];
-                v[k] = *reinterpret_cast<const uint2*>(slot_o + slot_o_index<D>(sl, ROWS, lr, d0));
+                for (int k = 0; k < kCombineSlots; ++k) {
+                    const int64_t sl = slot0 + min(s0 + k, ns - 1);
+                    lse[k] = slot_lse[sl * ROWS + lr];
+                    v[k] = *reinterpret_cast<const uint2*>(slot_o + slot_o_index<D>(sl, ROWS, lr, d0));
+                }
+#pragma unroll
+                for (int k = 0; k < kCombineSlots; ++k) {
+                    const bool in = s0 + k < ns;
+                    lse[k] = in ? lse[k] : -INFINITY;
+                    o[k] = in ? f32x4_t{bf16_lo(v[k].x), bf16_hi(v[k].x), bf16_lo(v[k].y), bf16_hi(v[k].y)}
+                              : f32x4_t{0.f, 0.f, 0.f, 0.f};
+                }
+                float m = M;
+#pragma unroll
+                for (int k = 0; k < kCombineSlots; ++k) m = fmaxf(m, lse[k]);
+                if (m == -INFINITY) continue;
+                // rescale what earlier rounds summed (nothing yet: M = -inf gives 0)
+                const float r = __builtin_amdgcn_exp2f(M - m);
+                L *= r;
+                acc *= r;
+#pragma unroll
+                for (int k = 0; k < kCombineSlots; ++k) {
+                    const float f = lse[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(lse[k] - m);
+                    L += f;
+                    acc += f * o[k];
+                }
+                M = m;
             }
-#pragma unroll
-            for (int k = 0; k < kCombineSlots; ++k) {
-                const bool in = s0 + k < ns;
-                lse[k] = in ? lse[k] : -INFINITY;
-                o[k] = in ? f32x4_t{bf16_lo(v[k].x), bf16_hi(v[k].x), bf16_lo(v[k].y), bf16_hi(v[k].y)}
-                          : f32x4_t{0.f, 0.f, 0.f, 0.f};
-            }
-            float m = M;
-#pragma unroll
-            for (int k = 0; k < kCombineSlots; ++k) m = fmaxf(m, lse[k]);
-            if (m == -INFINITY) continue;
-            // rescale what earlier rounds summed (nothing yet: M = -inf gives 0)
-            const float r = __builtin_amdgcn_exp2f(M - m);
-            L *= r;
-            acc *= r;
-#pragma unroll
-            for (int k = 0; k < kCombineSlots; ++k) {
-                const float f = lse[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(lse[k] - m);
-                L += f;
-                acc += f * o[k];
-            }
-            M = m;
         }
+        if constexpr (SG > 1) {
+            // slot groups 1 .. SG - 1 hand their sums to group 0, which merges
+            // them in ascending order
+            __shared__ float sm[SG][2][kCombineThreads / SG];
+            __shared__ f32x4_t so[SG][kCombineThreads / SG];
+            sm[sg][0][item] = M;
+            sm[sg][1][item] = L;
+            so[sg][item] = acc;
+            __syncthreads();
+            if (sg == 0) {
+                float m = M;
+#pragma unroll
+                for (int k = 1; k < SG; ++k) m = fmaxf(m, sm[k][0][item]);
+                if (m != -INFINITY) {
+                    const float r = __builtin_amdgcn_exp2f(M - m);
+                    L *= r;
+                    acc *= r;
+#pragma unroll
+                    for (int k = 1; k < SG; ++k) {
+                        const float f = __builtin_amdgcn_exp2f(sm[k][0][item] - m);
+                        L += f * sm[k][1][item];
+                        acc += f * so[k][item];
+                    }
+                }
+                M = m;
+            }
+            __syncthreads();  // before the next pass writes them again
+        }
+        if (sg != 0 || !in_row) continue;
         if (M != -INFINITY) {
             L += sink_term(a.sinks, g * a.group + rr % a.group, M);
             acc *= 1.f / L;
         }
+        const int j = rr / a.group, gh = rr - j * a.group;
+        const int64_t hrow = (int64_t)(rq.q0 + j) * a.hq + g * a.group + gh;
+        *reinterpret_cast<uint2*>(out + hrow * D + d0) =
+            make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
     }
-    const int j = rr / a.group, gh = rr - j * a.group;
-    const int64_t hrow = (int64_t)(rq.q0 + j) * a.hq + g * a.group + gh;
-    *reinterpret_cast<uint2*>(out + hrow * D + d0) =
-        make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
 }
 
 // ------------------------------------------------------------------ combine
@@ -1170,6 +1444,7 @@ struct AttnPlan {
         int rg_max;           // row groups per (request, KV head)
         int nwg;              // persistent workgroups
         int spb;              // fixed units per workgroup (0: equal shares)
+        bool whole;           // one workgroup per pair
         int rows_lo, rows_hi; // requests with Hq/Hkv * n_i in [rows_lo, rows_hi]
         int64_t slots;        // partial slots
         size_t off;           // workspace offset of the class's arrays
@@ -1194,20 +1469,47 @@ constexpr int kShortClassRows = 48;
 // than the balance gains).
 constexpr int64_t kOversubUnits = 4096;
 
-// KV blocks in flight per workgroup.  Three (a 32 KiB ring at D = 128) lets
-// four workgroups share a compute unit's 160 KiB of LDS; the four-wavefront
-// two-tile shape runs two workgroups per compute unit (its registers allow no
-// more) and takes five.  More workgroups per compute unit beat deeper rings:
-// each workgroup advances one block per barrier, so the per-block latency of
-// one workgroup is what more workgroups hide.
-constexpr int prefetch_depth(int d, int nw, int tpw) { return d == 128 && nw == 4 && tpw == 2 ? 5 : 3; }
+// Slots a pair of the longest length is cut into at most (with the resident
+// workgroups it is often fewer); no workgroup takes fewer than two blocks.
+// More workgroups shorten the walk of a small batch, but each adds a slot per
+// pair that the merge reads.  One request of 95 blocks on eight KV heads, walk and merge together:
+// 24.6 us with a workgroup per block (95 slots a pair), 13.9 / 13.1 / 13.5 /
+// 14.4 us with at least 2 / 4 / 6 / 8 blocks per workgroup; 32 blocks: 9.5 us
+// with 2, 10.7 with 4; 251 blocks: 19.7, 17.3 and with 12 blocks 15.1 us.
+constexpr int kSlotsPerPair = 24;
+
+// Whether a launch gives every pair to one workgroup: no schedule scan, no
+// partial slots and no merge launch, at the price of a walk as long as the
+// longest pair.  The walk of one workgroup takes 0.28 us per block on an idle
+// chip, the schedule, the slots and the merge about 6 us, so up to 16 blocks
+// whole pairs are always faster (8 KV heads of one request, 16 blocks: 10.2
+// against 10.7 us, 32 blocks 14.7 against 9.5 us).  Where the pairs fill the
+// compute units the walk is not longer than a share of the batch's: 256 pairs
+// of 32 / 63 blocks 16.5 / 31.4 against 23.3 / 37.6 us, 1024 pairs of 63
+// blocks 99 against 106 us (head dim 128) and 63 against 89 us (head dim 64).
+// In between the line rises with the pairs.  From 64 blocks on the
+// one-wavefront shapes take over, and a pair would be one wavefront's alone.
+bool whole_pairs(int64_t nb_max, int64_t pairs, int64_t cus) {
+    return nb_max <= std::min<int64_t>(63, 16 + 48 * pairs / cus);
+}
+
+// LDS stages (blocks) of a workgroup's ring.  A step computes two of them while
+// the others load.  Five (40 KiB at D = 128, 20 KiB at D = 64) let four (eight)
+// workgroups share a compute unit's 160 KiB of LDS, which is why the schedule
+// scan borrows the last stage instead of LDS of its own.  The four-wavefront
+// two-tile shape fits three workgroups by its registers and takes six.  More
+// workgroups per compute unit beat deeper rings (six stages and three
+// workgroups: 985 against 860 us on 4.6 GB at D = 64), and with four stages a
+// step finds nothing in flight behind its own blocks (284 against 239 us on
+// 1.2 GB at D = 128).
+constexpr int ring_stages(int d, int nw, int tpw) { return d == 128 && nw == 4 && tpw == 2 ? 6 : 5; }
 
 // The kernel shapes a plan may choose: head dim, wavefronts per workgroup,
 // 16-row tiles per wavefront.  with_shape calls f(Shape<...>{}) for the
 // matching entry and returns false if there is none.
 template <int D_, int NW_, int TPW_>
 struct Shape {
-    static constexpr int D = D_, NW = NW_, TPW = TPW_, PD = prefetch_depth(D_, NW_, TPW_);
+    static constexpr int D = D_, NW = NW_, TPW = TPW_, NS = ring_stages(D_, NW_, TPW_);
 };
 
 template <typename F>
@@ -1235,7 +1537,7 @@ bool with_shape(int d, int nw, int tpw, F&& f) {
 
 template <typename S, bool APPEND = false>
 constexpr auto persist_kernel() {
-    return attn_persist<S::D, S::NW, S::TPW, S::PD, APPEND>;
+    return attn_persist<S::D, S::NW, S::TPW, S::NS, APPEND>;
 }
 
 int validate(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
@@ -1335,11 +1637,17 @@ int plan_class(const verify_attn_params* p, int64_t rows, int64_t nb_max, int ro
                 res = append ? resident_wgs<decltype(sh), true>() : resident_wgs<decltype(sh)>();
             }))
             return VERIFY_EUNSUPPORTED;
-        const int64_t resident = (int64_t)device_cus() * res;
+        const int64_t apart = std::max<int64_t>(2, (nb_max + kSlotsPerPair - 1) / kSlotsPerPair);
+        const int64_t resident = std::min<int64_t>((int64_t)device_cus() * res, (units_max + apart - 1) / apart);
         const int64_t mult = std::min<int64_t>(8, std::max<int64_t>(1, units_max / resident / kOversubUnits));
         c.nwg = (int)(resident * mult);
     }
     c.slots = pairs + c.nwg;
+    if (c.spb == 0 && whole_pairs(nb_max, pairs, device_cus())) {
+        c.whole = true;
+        c.nwg = (int)pairs;
+        c.slots = 0;
+    }
     c.unit_bytes = align_up(sizeof(int32_t) * ((size_t)std::max(1, p->num_seqs) + 1), 256);
     c.slot_o_bytes = align_up((size_t)c.slots * per * p->head_dim * sizeof(uint16_t), 256);
     c.slot_lse_bytes = align_up((size_t)c.slots * per * sizeof(float), 256);
@@ -1415,7 +1723,7 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
                     int max_rows, hipStream_t stream) {
     return with_shape(head_dim, pl.nw, pl.tpw, [&](auto sh) {
         using S = decltype(sh);
-        if (!a.inline_sched)
+        if (!a.inline_sched && !a.whole)
             hipLaunchKernelGGL((attn_schedule<S::D>), dim3(1), dim3(1024), 0, stream, a, m.q_start,
                                m.seq_lens, m.unit_start, m.out);
         if (m.k_new)
@@ -1426,15 +1734,21 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
             hipLaunchKernelGGL(persist_kernel<S>(), dim3(a.nwg), dim3(S::NW * kWave), 0, stream, a,
                                m.q, m.kc, m.vc, m.block_tables, m.seq_lens, m.q_start, m.unit_start,
                                m.out, m.slot_o, m.slot_lse, nullptr, nullptr);
+        if (a.whole) return;
         const int64_t pairs = (int64_t)a.num_seqs * a.hkv * a.rg_max;
-        constexpr int RPB = kCombineThreads / (S::D / 4);
         // rows of a row group: at most rows_per_group, at most G * max_q_len
         const int group_rows = std::max(1, std::min(a.rows_per_group, max_rows));
-        const unsigned chunks = (unsigned)((group_rows + RPB - 1) / RPB);
-        if (pairs > 0)
-            hipLaunchKernelGGL((attn_combine_slots<S::D>), dim3((unsigned)pairs, chunks),
+        auto combine = [&](auto sg) {
+            constexpr int SG = decltype(sg)::value, RPB = kCombineThreads / (S::D / 4) / SG;
+            const unsigned chunks = (unsigned)((group_rows + RPB - 1) / RPB);
+            hipLaunchKernelGGL((attn_combine_slots<S::D, SG>), dim3((unsigned)pairs, chunks),
                                dim3(kCombineThreads), 0, stream, a, m.seq_lens, m.q_start,
                                m.unit_start, m.slot_o, m.slot_lse, m.out);
+        };
+        if (pairs <= 0) return;
+        // more than a round of slots per pair: four thread groups share a row
+        if (a.nwg > kCombineSlots * pairs) combine(std::integral_constant<int, 4>{});
+        else combine(std::integral_constant<int, 1>{});
     });
 }
 
@@ -1532,6 +1846,7 @@ int attention_call(const verify_attn_params* params, int32_t total_q, int32_t ma
             a.rg_max = c.rg_max;
             a.nwg = c.nwg;
             a.spb = c.spb;
+            a.whole = c.whole;
             a.rows_lo = c.rows_lo;
             a.rows_hi = c.rows_hi;
             const int64_t class_rows = std::min<int64_t>(max_rows, c.rows_hi);
@@ -1617,7 +1932,7 @@ extern "C" int verify_attention_plan(const verify_attn_params* params, int32_t t
             d[0] = c.nwg;
             d[1] = c.nw * c.tpw * 16;
             d[2] = c.rg_max;
-            d[3] = c.spb;
+            d[3] = c.whole ? -1 : c.spb;
         }
         info[10] = pl.nclass > 1 ? pl.cls[0].rows_hi : INT32_MAX;
     } else {
