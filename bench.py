@@ -123,7 +123,7 @@ def summarize_pmc(fetch_csv: str, write_csv: str, workload: str) -> None:
     # call).  A call launches each of them once per row class and layer, with a
     # grid of its own, so they are told apart by template arguments and grid;
     # the fused append's kernels (a side call) are not part of it.
-    call_kernels = ("attn_schedule", "attn_persist", "attn_combine_slots", "attn_valu", "attn_combine")
+    call_kernels = ("attn_schedule", "attn_persist", "attn_combine_slots", "attn_f32", "attn_combine")
 
     def per_kernel(path, counter):
         by_dispatch = collections.defaultdict(float)

@@ -183,7 +183,7 @@ int verify_attention_append(const verify_attn_params *params, int32_t total_q, i
  * kernel fits fewer per compute unit; it is not described here.
  *
  *   info     int32[VERIFY_ATTN_PLAN_INFO], written in full (unused entries 0)
- *   info[0]  1: bf16 persistent MFMA schedule, 0: fp32 split-K VALU kernel
+ *   info[0]  1: bf16 persistent MFMA schedule, 0: fp32 split-K kernel
  *   bf16:    info[5] row classes (1 or 2), one persistent launch each; a
  *            request whose Hq/Hkv * n_i is at most info[10] is in class 0,
  *            the others in class 1.  Class 0 in info[1..4], class 1 in

@@ -30,7 +30,6 @@ namespace {
 
 constexpr int kAttnWaves = 4;
 constexpr int kAttnThreads = kAttnWaves * kWave;
-constexpr int kValuRows = 8;  // query rows per VALU work item
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct AttnArgs {
@@ -48,7 +47,8 @@ struct AttnArgs {
     const void* v_new;
     int num_seqs, hq, hkv, group, max_blocks, num_blocks, window, max_seq_len;
     float scale_log2;  // softmax scale * log2(e): scores live in the log2 domain
-    int split_blocks, max_splits, row_groups;
+    int split_blocks, max_splits, row_groups, rows_per_group;
+    int split0;  // first split of the launch
 };
 
 // A head's attention sink is one more logit in each row's softmax with a zero
@@ -81,203 +81,294 @@ __device__ __forceinline__ SeqGeom seq_geom(const AttnArgs& a, int i) {
     return g;
 }
 
-// ------------------------------------------------------------------ VALU path
+// ------------------------------------------------------------------ fp32 storage
 //
-// Lane layout inside a wavefront, per 16-token block:
-//   scores  lane = t + 16*dq: key t, dimension quarter dq; the partial dot
-//           products of the four quarters are summed with two xor-shuffles;
-//   output  lane owns D/64 consecutive output dimensions, reading V^T rows
-//           (16 keys of one dimension are contiguous in the V layout) and the
-//           16 probabilities of the block broadcast through readlane.
+// A work item is (request, KV head, row group, split), its four wavefronts take
+// the split's blocks round-robin, each with an online softmax of its own, and
+// merge through LDS at the end.  Both contractions run on v_mfma_f32_16x16x4_f32
+// (fp32 products and sums), in 16-row tiles, RT of them per work item:
+//   S^T = K Q^T    A = K (16 keys x 4 dims: one float of key l16 per lane), B =
+//                  Q^T; lane 16 lg + l16 takes the 16-byte chunks lg, lg + 4, ...
+//                  of its key, so each K load of a wavefront is one contiguous
+//                  KiB, straight into operand registers; the result lane holds
+//                  keys 4 lg .. 4 lg + 3 of row l16;
+//   O^T += V^T P^T A = V^T (dim l16 of a 16-dim tile; a lane's 16 bytes of V^T are
+//                  its keys 4 lg .. 4 lg + 3), B = P^T, which the S registers
+//                  already are: product j takes key 4 lg + j of every lane group.
+// Nothing but the query rows goes through LDS.  The next block's K loads leave
+// once the scores are done and its V loads once the output is, so a wavefront
+// always has 8 KiB in flight (D = 128).
+// What bounds it: a block costs a SIMD 2048 cycles of products per tile at D =
+// 128 against 16 KiB of K and V, so HBM up to about two tiles, the fp32 products
+// beyond.  Against the vector kernel before it (eight rows per work item, each
+// walking the keys again): 16 requests of 1k to 8k tokens, 20 rows, 604 MB 604 ->
+// 155 us (3.9 TB/s); 8 requests of 2k to 16k tokens, 72 rows 1411 -> 316 us.
+// The scores are summed in four chains that are added at the end: shorter sums,
+// and no product waits for the one before it.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// callers' fp32 tensors and the workspace need only be aligned to a float
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+
+// Maximum of v over lanes l, l ^ 16, l ^ 32, l ^ 48 (the four lanes that hold
+// one row of an MFMA result tile).  Each permlane swap exchanges half of the
+// wavefront between its two operands; with both operands equal to v, the two
+// results of lane l are v of l and of l ^ 32 (l ^ 16), in some order.
+__device__ __forceinline__ float row_max_4lanes(float v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const float m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Softmax weights may exceed 1 by up to this factor (log2) before the stored
+// row maximum is raised.
+constexpr float kSlackLog2 = 8.f;
+
+// Whether block b has a key that some row of a request must not see: keys past
+// its first row's position p_first, or (window) keys below its last row's window.
+__device__ __forceinline__ bool block_needs_mask(int b, int p_first, int S, int window) {
+    return (b * kBlockTokens + kBlockTokens - 1 > p_first) ||
+           (window > 0 && b * kBlockTokens < S - window);
+}
+
+// Waves per SIMD that the registers of RT tiles leave room for (an output tile
+// takes D / 4 registers, the K and V operands D / 2).
+constexpr int f32_waves(int d, int rt) { return d == 64 ? (rt == 1 ? 4 : rt == 2 ? 3 : 2) : rt == 1 ? 3 : 2; }
+// Row tiles a work item takes at most: the most that fit 256 registers.
+constexpr int f32_max_tiles(int d) { return d == 64 ? 4 : 3; }
+
 // APPEND: the fused KV append (verify_attention_append).  Keys and values of
 // the request's new tokens are read from k_new / v_new instead of the cache,
 // and the work items of row group 0 (splits cover disjoint blocks) store them
 // into the cache as well.
-template <typename T, int D, bool APPEND>
-__global__ __launch_bounds__(kAttnThreads) void attn_valu(AttnArgs a) {
-    constexpr int X = Storage<T>::kPer16B;  // elements per 16 bytes
-    constexpr int NC = D / X;               // 16-byte chunks per key
-    constexpr int CPL = NC / 4;             // chunks per lane
-    constexpr int DPL = D / kWave;          // output dimensions per lane
-    constexpr int RB = kValuRows;
-    constexpr int VCH = kBlockTokens / X;   // 16-byte chunks per V^T row
-    static_assert(NC % 4 == 0 && D % kWave == 0, "head_dim");
+template <int D, int RT, bool APPEND>
+__global__ __launch_bounds__(kAttnThreads, f32_waves(D, RT)) void attn_f32(AttnArgs a) {
+    constexpr int NU = D / 16;  // 16-byte K chunks per lane; 16-dim output tiles
+    constexpr int ROWS = RT * 16;
+    constexpr int QN = RT * NU * kWave, MN = kAttnWaves * NU * kWave;
 
-    const int i = blockIdx.z;
-    const int kvh = blockIdx.y / a.row_groups;
-    const int rg = blockIdx.y - kvh * a.row_groups;
-    const int s = blockIdx.x;
+    // Grid (pair within the request + pairs * split, request): workgroups go round
+    // the XCDs and their shader engines in launch order, so the heads of a block
+    // are read at the same time and the empty splits of short requests come
+    // together.  With the split index fastest and a multiple of eight splits an
+    // XCD got the same splits of every pair, and the XCDs of the high ones
+    // nothing from short requests (16 requests of 1k to 8k tokens, 16 splits:
+    // 182 -> 155 us).
+    const int i = blockIdx.y;
+    const int pairs = a.hkv * a.row_groups;
+    const int pair = blockIdx.x % pairs;
+    const int s = a.split0 + blockIdx.x / pairs;
+    const int kvh = pair / a.row_groups;
+    const int rg = pair - kvh * a.row_groups;
     const SeqGeom sg = seq_geom(a, i);
     const int rows_total = a.group * sg.n;
-    const int r0 = rg * RB;
+    const int r0 = rg * ROWS;
     if (r0 >= rows_total || s >= sg.nsplit) return;
     const int sb = sg.b_lo + s * a.split_blocks;
     const int se = min(sg.b_hi, sb + a.split_blocks);
-    const int nrows = min(RB, rows_total - r0);
+    const int tiles = min(RT, (rows_total - r0 + 15) / 16);  // that hold rows
 
-    __shared__ float q_s[RB][D];
-    __shared__ float merge_o[kAttnWaves][RB][D];
-    __shared__ float merge_m[kAttnWaves][RB];
-    __shared__ float merge_l[kAttnWaves][RB];
+    // the query rows as B operands, one KiB per (tile, chunk); after the walk
+    // the wavefronts' outputs of one tile
+    __shared__ f32x4_t lds[QN > MN ? QN : MN];
+    __shared__ float merge_m[kAttnWaves][ROWS];
+    __shared__ float merge_l[kAttnWaves][ROWS];
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
-    const int w = tid / kWave;
-    const T* qp = static_cast<const T*>(a.q);
-    for (int e = tid; e < RB * D; e += kAttnThreads) {
-        const int r = e / D, d = e - r * D;
-        float v = 0.f;
-        if (r < nrows) {
-            const int rr = r0 + r;
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int l16 = lane & 15, lg = lane >> 4;
+
+    const float* qp = static_cast<const float*>(a.q);
+    for (int e = tid; e < QN; e += kAttnThreads) {
+        const int rr = r0 + e / (NU * kWave) * 16 + l16;
+        const int chunk = lg + 4 * (e / kWave % NU);
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+        if (rr < rows_total) {
             const int j = rr / a.group, gh = rr - j * a.group;
-            const int64_t qrow = sg.q0 + j;
-            v = Storage<T>::load(qp, (qrow * a.hq + kvh * a.group + gh) * D + d) * a.scale_log2;
+            v = *reinterpret_cast<const f32x4u_t*>(
+                qp + ((int64_t)(sg.q0 + j) * a.hq + kvh * a.group + gh) * D + chunk * 4);
+            v *= a.scale_log2;
         }
-        q_s[r][d] = v;
+        lds[e] = v;
     }
     __syncthreads();
 
-    float m_r[RB], l_r[RB], o[RB][DPL];
-    int pos_r[RB], lo_r[RB];
+    float m[RT], l[RT];
+    f32x4_t o[RT][NU];
+    int pos[RT], lo[RT];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        m_r[r] = -INFINITY;
-        l_r[r] = 0.f;
+    for (int r = 0; r < RT; ++r) {
+        m[r] = -INFINITY;
+        l[r] = 0.f;
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) o[r][e] = 0.f;
-        const int j = (r0 + r) / a.group;
-        pos_r[r] = sg.S - sg.n + j;
-        lo_r[r] = a.window > 0 ? pos_r[r] - a.window + 1 : 0;
+        for (int t = 0; t < NU; ++t) o[r][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        pos[r] = sg.S - sg.n + (r0 + r * 16 + l16) / a.group;
+        lo[r] = a.window > 0 ? pos[r] - a.window + 1 : 0;
     }
 
-    const int t = lane & 15, dq = lane >> 4;
-    const T* kc = static_cast<const T*>(a.kc);
-    const T* vc = static_cast<const T*>(a.vc);
+    const float* kc = static_cast<const float*>(a.kc);
+    const float* vc = static_cast<const float*>(a.vc);
     const int64_t tile = (int64_t)kBlockTokens * D;
     const int32_t* btab = a.block_tables + (int64_t)i * a.max_blocks;
     // APPEND: new-token positions the walk reaches, and the first row's position
     const int p0 = sg.s_raw - sg.n;
     const int nlo = max(p0, 0), nhi = min(sg.s_raw, sg.S);
-    const T* knew = static_cast<const T*>(a.k_new);
-    const T* vnew = static_cast<const T*>(a.v_new);
+    const float* knew = static_cast<const float*>(a.k_new);
+    const float* vnew = static_cast<const float*>(a.v_new);
+    auto holds_new = [&](int b) { return APPEND && b * kBlockTokens < nhi && (b + 1) * kBlockTokens > nlo; };
 
-    for (int b = sb + w; b < se; b += kAttnWaves) {
-        const int phys = btab[b];
-        if (phys < 0 || phys >= a.num_blocks) continue;
-        const T* ktile = kc + ((int64_t)phys * a.hkv + kvh) * tile;
-        const T* vtile = vc + ((int64_t)phys * a.hkv + kvh) * tile;
-        const int tk = b * kBlockTokens + t;
-        // APPEND: a new token's key comes from k_new (its row's 16-byte chunks)
-        const bool knew_t = APPEND && tk >= nlo && tk < nhi;
-        const int64_t nrow = (int64_t)sg.q0 + (tk - p0);
-        float kf[CPL * X];
+    f32x4_t kf[NU], vf[NU];
+    auto load_k = [&](int b, int phys) {
+        const float* kt = kc + ((int64_t)phys * a.hkv + kvh) * tile + lane * 4;
 #pragma unroll
-        for (int u = 0; u < CPL; ++u) {
-            const int c16 = dq * CPL + u;
-            const T* kp = knew_t ? knew + (nrow * a.hkv + kvh) * D + c16 * X
-                                 : ktile + (c16 * kBlockTokens + t) * X;
-            const uint4 kraw = ld16(kp);
-            if (APPEND && knew_t && rg == 0)
-                *reinterpret_cast<uint4*>(const_cast<T*>(ktile) + (c16 * kBlockTokens + t) * X) = kraw;
-            unpack16(kraw, &kf[u * X], T());
-        }
-        float vf[DPL][kBlockTokens];
+        for (int u = 0; u < NU; ++u) kf[u] = *reinterpret_cast<const f32x4_t*>(kt + u * (kWave * 4));
+        if (holds_new(b)) {
+            const int tk = b * kBlockTokens + l16;
+            if (tk >= nlo && tk < nhi) {
+                const float* kn = knew + ((int64_t)(sg.q0 + (tk - p0)) * a.hkv + kvh) * D + lg * 4;
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) {
-            const T* vrow = vtile + (lane * DPL + e) * kBlockTokens;
-#pragma unroll
-            for (int c = 0; c < VCH; ++c) unpack16(ld16(vrow + c * X), &vf[e][c * X], T());
-        }
-        if (APPEND && b * kBlockTokens < nhi && (b + 1) * kBlockTokens > nlo) {
-            // the new tokens' values: dimension lane * DPL + e of row
-            // q0 + (position - p0), for the block's new positions
-#pragma unroll
-            for (int tt = 0; tt < kBlockTokens; ++tt) {
-                const int pos = b * kBlockTokens + tt;
-                if (pos < nlo || pos >= nhi) continue;
-                const int64_t vrow_new = ((int64_t)sg.q0 + (pos - p0)) * a.hkv + kvh;
-#pragma unroll
-                for (int e = 0; e < DPL; ++e) {
-                    const int d = lane * DPL + e;
-                    const T v = vnew[vrow_new * D + d];
-                    vf[e][tt] = Storage<T>::load(&v, 0);
-                    if (rg == 0) const_cast<T*>(vtile)[d * kBlockTokens + tt] = v;
+                for (int u = 0; u < NU; ++u) {
+                    kf[u] = *reinterpret_cast<const f32x4u_t*>(kn + u * 16);
+                    if (rg == 0) *reinterpret_cast<f32x4_t*>(const_cast<float*>(kt) + u * (kWave * 4)) = kf[u];
                 }
             }
         }
+    };
+    auto load_v = [&](int b, int phys) {
+        const float* vt = vc + ((int64_t)phys * a.hkv + kvh) * tile + l16 * kBlockTokens + lg * 4;
+#pragma unroll
+        for (int t = 0; t < NU; ++t) vf[t] = *reinterpret_cast<const f32x4_t*>(vt + t * (kWave * 4));
+        if (holds_new(b)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int tk = b * kBlockTokens + lg * 4 + j;
+                if (tk < nlo || tk >= nhi) continue;
+                const float* vn = vnew + ((int64_t)(sg.q0 + (tk - p0)) * a.hkv + kvh) * D + l16;
+#pragma unroll
+                for (int t = 0; t < NU; ++t) {
+                    vf[t][j] = vn[t * 16];
+                    if (rg == 0) const_cast<float*>(vt)[t * (kWave * 4) + j] = vf[t][j];
+                }
+            }
+        }
+    };
 
+    // the ids of the wavefront's next 64 blocks, one per lane; blocks whose id
+    // is out of range are left out
+    for (int base = sb + w; base < se; base += kAttnWaves * kWave) {
+        const int bl = base + kAttnWaves * lane;
+        const int id = bl < se ? btab[bl] : -1;
+        uint64_t todo = __ballot(id >= 0 && id < a.num_blocks);
+        if (todo == 0) continue;
+        int at = __builtin_ctzll(todo);
+        int phys = __builtin_amdgcn_readlane(id, at);
+        int b = base + kAttnWaves * at;
+        load_k(b, phys);
+        load_v(b, phys);
+        while (true) {
+            todo &= todo - 1;
+            const int at2 = todo ? __builtin_ctzll(todo) : at;
+            const int b2 = base + kAttnWaves * at2;
+            phys = __builtin_amdgcn_readlane(id, at2);
+            const bool masked = block_needs_mask(b, sg.S - sg.n, sg.S, a.window);
+            f32x4_t p[RT];
+            // keeps the query operands in LDS: hoisted out of the loop they would
+            // take D / 4 registers per tile and spill
+            int ql = lane;
+            asm volatile("" : "+v"(ql));
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            if (r >= nrows) break;
-            float sc = 0.f;
+            for (int r = 0; r < RT; ++r) {
+                if (r >= tiles) break;
+                f32x4_t acc[4];
 #pragma unroll
-            for (int u = 0; u < CPL; ++u) {
-                const float* qv = &q_s[r][(dq * CPL + u) * X];
+                for (int c = 0; c < 4; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < X; ++e) sc = fmaf(qv[e], kf[u * X + e], sc);
+                for (int u = 0; u < NU; ++u) {
+                    const f32x4_t qf = lds[(r * NU + u) * kWave + ql];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][e], qf[e], acc[e], 0, 0, 0);
+                }
+                p[r] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             }
-            sc += __shfl_xor(sc, 16);
-            sc += __shfl_xor(sc, 32);
-            const bool vis = tk <= pos_r[r] && tk >= lo_r[r];
-            sc = vis ? sc : -INFINITY;
-            const float mx = wave_max_xor(sc, 16);
-            const float mnew = fmaxf(m_r[r], mx);
-            const float muse = mnew == -INFINITY ? 0.f : mnew;
-            const float alpha = exp2f(m_r[r] - muse);
-            const float pt = exp2f(sc - muse);
-            l_r[r] = l_r[r] * alpha + wave_sum_xor(pt, 16);
-            m_r[r] = mnew;
-            float acc[DPL];
+            if (todo) load_k(b2, phys);
 #pragma unroll
-            for (int e = 0; e < DPL; ++e) acc[e] = o[r][e] * alpha;
+            for (int r = 0; r < RT; ++r) {
+                if (r >= tiles) break;
+                if (masked) {
 #pragma unroll
-            for (int tt = 0; tt < kBlockTokens; ++tt) {
-                const float ptt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pt), tt));
+                    for (int j = 0; j < 4; ++j) {
+                        const int tk = b * kBlockTokens + lg * 4 + j;
+                        p[r][j] = tk <= pos[r] && tk >= lo[r] ? p[r][j] : -INFINITY;
+                    }
+                }
+                const float mx = fmaxf(fmaxf(p[r][0], p[r][1]), fmaxf(p[r][2], p[r][3]));
+                if (__any(mx > m[r] + kSlackLog2)) {
+                    const float mnew = fmaxf(m[r], row_max_4lanes(mx));
+                    const float alpha = exp2f(m[r] - (mnew == -INFINITY ? 0.f : mnew));
+                    l[r] *= alpha;
 #pragma unroll
-                for (int e = 0; e < DPL; ++e) acc[e] = fmaf(ptt, vf[e][tt], acc[e]);
+                    for (int t = 0; t < NU; ++t) o[r][t] *= alpha;
+                    m[r] = mnew;
+                }
+                const float muse = m[r] == -INFINITY ? 0.f : m[r];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) p[r][j] = exp2f(p[r][j] - muse);
+                l[r] += (p[r][0] + p[r][1]) + (p[r][2] + p[r][3]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int t = 0; t < NU; ++t)
+                        o[r][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][j], p[r][j], o[r][t], 0, 0, 0);
             }
-#pragma unroll
-            for (int e = 0; e < DPL; ++e) o[r][e] = acc[e];
+            if (todo == 0) break;
+            load_v(b2, phys);
+            at = at2;
+            b = b2;
         }
     }
 
-    // merge the four wavefronts' states
+    // merge the four wavefronts' states, one row tile at a time
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        if (lane == 0) {
-            merge_m[w][r] = m_r[r];
-            merge_l[w][r] = l_r[r];
+    for (int r = 0; r < RT; ++r) {
+        l[r] += __shfl_xor(l[r], 16);
+        l[r] += __shfl_xor(l[r], 32);
+        if (lg == 0) {
+            merge_m[w][r * 16 + l16] = m[r];
+            merge_l[w][r * 16 + l16] = l[r];
         }
-#pragma unroll
-        for (int e = 0; e < DPL; ++e) merge_o[w][r][lane * DPL + e] = o[r][e];
     }
     __syncthreads();
-    T* outp = static_cast<T*>(a.out);
-    for (int e = tid; e < nrows * D; e += kAttnThreads) {
-        const int r = e / D, d = e - r * D;
-        float M = -INFINITY;
+    float* outp = static_cast<float*>(a.out);
 #pragma unroll
-        for (int ww = 0; ww < kAttnWaves; ++ww) M = fmaxf(M, merge_m[ww][r]);
-        float L = 0.f, O = 0.f;
-        if (M != -INFINITY) {
+    for (int r = 0; r < RT; ++r) {
+        float M = -INFINITY, L = 0.f;
 #pragma unroll
-            for (int ww = 0; ww < kAttnWaves; ++ww) {
-                const float f = exp2f(merge_m[ww][r] - M);
-                L = fmaf(f, merge_l[ww][r], L);
-                O = fmaf(f, merge_o[ww][r][d], O);
-            }
-        }
-        const int rr = r0 + r;
-        const int j = rr / a.group, gh = rr - j * a.group;
-        const int64_t hrow = (int64_t)(sg.q0 + j) * a.hq + kvh * a.group + gh;
-        if (sg.nsplit == 1) {
-            const float den = L + sink_term(a.sinks, kvh * a.group + gh, M);
-            Storage<T>::store(outp, hrow * D + d, den > 0.f ? O / den : 0.f);
-        } else {
-            const float val = L > 0.f ? O / L : 0.f;
+        for (int ww = 0; ww < kAttnWaves; ++ww) M = fmaxf(M, merge_m[ww][r * 16 + l16]);
+        const float Muse = M == -INFINITY ? 0.f : M;
+#pragma unroll
+        for (int ww = 0; ww < kAttnWaves; ++ww)
+            L = fmaf(exp2f(merge_m[ww][r * 16 + l16] - Muse), merge_l[ww][r * 16 + l16], L);
+        const float f = exp2f(m[r] - Muse);
+        if (r > 0) __syncthreads();  // the tile before has been read
+#pragma unroll
+        for (int t = 0; t < NU; ++t) lds[(w * NU + t) * kWave + lane] = o[r][t] * f;
+        __syncthreads();
+        const int rr = r0 + r * 16 + l16;
+        if (rr < rows_total) {
+            const int j = rr / a.group, gh = rr - j * a.group;
+            const int64_t hrow = (int64_t)(sg.q0 + j) * a.hq + kvh * a.group + gh;
+            const float den = sg.nsplit == 1 ? L + sink_term(a.sinks, kvh * a.group + gh, M) : L;
             const int64_t pi = hrow * a.max_splits + s;
-            a.part_o[pi * D + d] = val;
-            if (d == 0) a.part_lse[pi] = L > 0.f ? M + log2f(L) : -INFINITY;
+            float* dst = sg.nsplit == 1 ? outp + hrow * D : a.part_o + pi * D;
+            for (int t = w; t < NU; t += kAttnWaves) {
+                f32x4_t O = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ww = 0; ww < kAttnWaves; ++ww) O += lds[(ww * NU + t) * kWave + lane];
+                *reinterpret_cast<f32x4u_t*>(dst + t * 16 + lg * 4) = den > 0.f ? O / den : f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+            if (sg.nsplit > 1 && w == 0 && lg == 0) a.part_lse[pi] = L > 0.f ? M + log2f(L) : -INFINITY;
         }
     }
 }
@@ -332,23 +423,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_valu(AttnArgs a) {
 // running max and rescale factor live in the lanes that own its scores.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-// Maximum of v over lanes l, l ^ 16, l ^ 32, l ^ 48 (the four lanes that hold
-// one row of an MFMA result tile).  Each permlane swap exchanges half of the
-// wavefront between its two operands; with both operands equal to v, the two
-// results of lane l are v of l and of l ^ 32 (l ^ 16), in some order.
-__device__ __forceinline__ float row_max_4lanes(float v) {
-    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    const float m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-
-// Softmax weights may exceed 1 by up to this factor (log2) before the stored
-// row maximum is raised.
-constexpr float kSlackLog2 = 8.f;
-
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(const uint4& v) { return __builtin_bit_cast(bf16x8_t, v); }
 
@@ -673,14 +748,6 @@ __device__ __forceinline__ void wait_blocks(int n) {
         if (n >= MAXN) wait_vmcnt<CPT * MAXN>();
         else wait_blocks<CPT, -1, MAXN - 1>(n);
     }
-}
-
-// Whether every row of the request sees every key of block b: the block lies
-// below the first row's position and, with a window, inside the last row's
-// window.
-__device__ __forceinline__ bool block_needs_mask(int b, int p_first, int S, int window) {
-    return (b * kBlockTokens + kBlockTokens - 1 > p_first) ||
-           (window > 0 && b * kBlockTokens < S - window);
 }
 
 // Global->LDS loads need about sixteen wavefronts per compute unit to reach
@@ -1321,9 +1388,14 @@ void attn_combine_slots(
 // One wavefront per (query row, q-head): log-sum-exp merge of the split
 // partials, O = sum_s 2^(lse_s - M) o_s / sum_s 2^(lse_s - M).  Also writes
 // the zero output of rows whose request has no key at all.
-template <typename T, int D>
+// The log-sum-exps of up to 64 splits are read together, one per lane, and the
+// partials eight at a time, all of a round's loads before their use: with one
+// load per split behind the test of its log-sum-exp the merge of 33 splits was a
+// chain of memory latencies (2560 rows: 19.9 us).
+template <int D>
 __global__ __launch_bounds__(kAttnThreads) void attn_combine(AttnArgs a, int total_q) {
     constexpr int DPL = D / kWave;
+    constexpr int kRound = 8;
     const int64_t item = (int64_t)blockIdx.x * kAttnWaves + threadIdx.x / kWave;
     if (item >= (int64_t)total_q * a.hq) return;
     const int lane = threadIdx.x & (kWave - 1);
@@ -1335,44 +1407,52 @@ __global__ __launch_bounds__(kAttnThreads) void attn_combine(AttnArgs a, int tot
         if (a.q_start[mid] <= row) lo = mid; else hi = mid - 1;
     }
     const SeqGeom sg = seq_geom(a, lo);
-    T* outp = static_cast<T*>(a.out);
-    {
-        // rows past the launch's reach (a request with more than max_q_len
-        // rows) are not computed: quiet NaN instead of stale memory
-        const int h = (int)(item - (int64_t)row * a.hq);
-        const int rr = (row - sg.q0) * a.group + h % a.group;
-        if (rr >= a.row_groups * kValuRows) {
+    float* outp = static_cast<float*>(a.out) + item * D + lane * DPL;
+    const int h = (int)(item - (int64_t)row * a.hq);
+    // rows past the launch's reach (a request with more than max_q_len rows) are
+    // not computed: quiet NaN instead of stale memory
+    if ((row - sg.q0) * a.group + h % a.group >= a.row_groups * a.rows_per_group) {
 #pragma unroll
-            for (int e = 0; e < DPL; ++e) Storage<T>::store(outp, item * D + lane * DPL + e, __builtin_nanf(""));
-            return;
-        }
+        for (int e = 0; e < DPL; ++e) outp[e] = __builtin_nanf("");
+        return;
     }
     if (sg.nsplit == 1) return;
     float acc[DPL];
 #pragma unroll
     for (int e = 0; e < DPL; ++e) acc[e] = 0.f;
-    float L = 0.f;
-    if (sg.nsplit > 1) {
-        const int64_t pi0 = item * a.max_splits;
-        float M = -INFINITY;
-        const int h = (int)(item - (int64_t)row * a.hq);
-        for (int s = 0; s < sg.nsplit; ++s) M = fmaxf(M, a.part_lse[pi0 + s]);
-        if (M != -INFINITY) {
-            for (int s = 0; s < sg.nsplit; ++s) {
-                const float lse = a.part_lse[pi0 + s];
-                if (lse == -INFINITY) continue;
-                const float f = exp2f(lse - M);
-                L += f;
-                const float* po = a.part_o + (pi0 + s) * D + lane * DPL;
+    float M = -INFINITY, L = 0.f;
+    for (int base = 0; base < sg.nsplit; base += kWave) {
+        const int64_t pi0 = item * a.max_splits + base;
+        const int ns = min(kWave, sg.nsplit - base);
+        const float lse = lane < ns ? a.part_lse[pi0 + lane] : -INFINITY;
+        const float mnew = fmaxf(M, wave_max_xor(lse, kWave));
+        if (mnew == -INFINITY) continue;
+        // rescale what earlier splits summed (nothing yet: M = -inf gives 0)
+        const float alpha = exp2f(M - mnew);
+        const float f = exp2f(lse - mnew);
+        L = L * alpha + wave_sum_xor(f, kWave);
 #pragma unroll
-                for (int e = 0; e < DPL; ++e) acc[e] = fmaf(f, po[e], acc[e]);
+        for (int e = 0; e < DPL; ++e) acc[e] *= alpha;
+        M = mnew;
+        const float* po = a.part_o + pi0 * D + lane * DPL;
+        for (int s0 = 0; s0 < ns; s0 += kRound) {
+            float v[kRound][DPL];
+#pragma unroll
+            for (int k = 0; k < kRound; ++k)
+#pragma unroll
+                for (int e = 0; e < DPL; ++e) v[k][e] = po[(int64_t)min(s0 + k, ns - 1) * D + e];
+#pragma unroll
+            for (int k = 0; k < kRound; ++k) {
+                // splits past the last have f = 0 (lse -inf); at 64 the lane wraps
+                const float fk = s0 + k < ns ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), s0 + k)) : 0.f;
+#pragma unroll
+                for (int e = 0; e < DPL; ++e) acc[e] = fmaf(fk, v[k][e], acc[e]);
             }
-            L += sink_term(a.sinks, h, M);
         }
     }
+    if (M != -INFINITY) L += sink_term(a.sinks, h, M);
 #pragma unroll
-    for (int e = 0; e < DPL; ++e)
-        Storage<T>::store(outp, item * D + lane * DPL + e, L > 0.f ? acc[e] / L : 0.f);
+    for (int e = 0; e < DPL; ++e) outp[e] = L > 0.f ? acc[e] / L : 0.f;
 }
 
 // ------------------------------------------------------------------ KV append
@@ -1431,14 +1511,15 @@ __global__ __launch_bounds__(kAppendThreads) void attn_kv_append(
 // ------------------------------------------------------------------ host side
 
 struct AttnPlan {
-    bool mfma;        // bf16 storage: persistent MFMA kernel; fp32 storage: VALU kernel
-    // VALU path
+    bool mfma;        // bf16 storage: persistent kernel; fp32 storage: split-K kernel
+    // fp32 path
     int split_blocks;
     int max_splits;
     int row_groups;
+    int tiles;        // 16-row tiles per work item
     size_t part_o_bytes;
     size_t part_lse_bytes;
-    // MFMA path: one persistent launch per row class
+    // bf16 path: one persistent launch per row class
     struct Class {
         int nw, tpw;          // wavefronts per workgroup, 16-row tiles per wavefront
         int rg_max;           // row groups per (request, KV head)
@@ -1654,6 +1735,17 @@ int plan_class(const verify_attn_params* p, int64_t rows, int64_t nb_max, int ro
     return VERIFY_OK;
 }
 
+// fp32 storage: a split is at most kF32SplitBlocks blocks (a partial row of D
+// floats per split is written and read again: 16 requests of 1k to 8k tokens take
+// 163 / 152 / 155 / 148 / 175 us at 16 / 24 / 32 / 48 / 64, and long splits leave
+// the last workgroups alone), shorter when the batch has fewer than kF32Items of
+// them (a workgroup per compute unit), down to a block per wavefront: one request
+// of 94 blocks 28 us at 32, under the call's host time from 16 down; two requests
+// of 3750 blocks on one KV head 63 / 45 / 38 / 39 / 56 us at 8 / 16 / 24 / 32 / 64.
+// From 262144 blocks on the items are held to about 8192.
+constexpr int kF32Items = 256;
+constexpr int kF32SplitBlocks = 32;
+
 int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
               int32_t max_seq_len, AttnPlan* out, bool append = false) {
     AttnPlan pl{};
@@ -1693,19 +1785,22 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
         }
         pl.total_bytes = off;
     } else {
+        // as few row groups as hold the tiles, the tiles spread evenly over them
+        const int64_t tiles = (rows + 15) / 16, most = f32_max_tiles(p->head_dim);
+        pl.row_groups = (int)std::min<int64_t>((tiles + most - 1) / most, 1 << 24);
+        pl.tiles = (int)((tiles + pl.row_groups - 1) / pl.row_groups);
         int sb = p->kv_split_blocks;
         if (sb == 0) {
-            // aim for about 8192 work items over the batch, at least 32 blocks per split
-            const int64_t total = (int64_t)std::max(1, p->num_seqs) * p->num_kv_heads * nb_max;
-            int64_t want = (total + 8191) / 8192;
-            want = std::max<int64_t>(32, (want + 3) / 4 * 4);
+            const int64_t total = (int64_t)std::max(1, p->num_seqs) * p->num_kv_heads * pl.row_groups * nb_max;
+            int64_t want = ((total + kF32Items - 1) / kF32Items + 3) / 4 * 4;
+            want = std::min<int64_t>(want, std::max<int64_t>(kF32SplitBlocks, (total / 8192 + 3) / 4 * 4));
             sb = (int)std::min<int64_t>(want, nb_max);
         }
         pl.split_blocks = std::max(1, sb);
         pl.max_splits = (int)((nb_max + pl.split_blocks - 1) / pl.split_blocks);
-        pl.row_groups = (int)((rows + kValuRows - 1) / kValuRows);
-        // grid (splits, KV heads x row groups, requests): y is a 16-bit dimension
-        if ((int64_t)p->num_kv_heads * pl.row_groups > 65535) return VERIFY_EUNSUPPORTED;
+        // grid (splits, KV heads x row groups, requests): y is a 16-bit dimension,
+        // and the call's limit is eight rows per row group
+        if ((int64_t)p->num_kv_heads * ((rows + 7) / 8) > 65535) return VERIFY_EUNSUPPORTED;
         if (pl.max_splits > 1) {
             const size_t items = (size_t)total_q * p->num_q_heads * pl.max_splits;
             pl.part_o_bytes = align_up(items * p->head_dim * sizeof(float), 256);
@@ -1752,17 +1847,27 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
     });
 }
 
-template <typename T, int D>
-void launch_valu(const AttnArgs& a, const AttnPlan& pl, int total_q, hipStream_t stream) {
-    dim3 grid(pl.max_splits, a.hkv * pl.row_groups, a.num_seqs);
-    if (a.k_new)
-        hipLaunchKernelGGL((attn_valu<T, D, true>), grid, dim3(kAttnThreads), 0, stream, a);
-    else
-        hipLaunchKernelGGL((attn_valu<T, D, false>), grid, dim3(kAttnThreads), 0, stream, a);
+template <int D>
+void launch_f32(AttnArgs a, const AttnPlan& pl, int total_q, hipStream_t stream) {
+    // a grid dimension holds fewer than 2^32 threads, 2^24 workgroups
+    const int pairs = a.hkv * pl.row_groups, step = ((1 << 24) - 1) / pairs;
+    dim3 grid(1, a.num_seqs);
+    auto walk = [&](auto rt) {
+        constexpr int RT = decltype(rt)::value;
+        if (a.k_new) hipLaunchKernelGGL((attn_f32<D, RT, true>), grid, dim3(kAttnThreads), 0, stream, a);
+        else hipLaunchKernelGGL((attn_f32<D, RT, false>), grid, dim3(kAttnThreads), 0, stream, a);
+    };
+    for (a.split0 = 0; a.split0 < pl.max_splits; a.split0 += step) {
+        grid.x = (unsigned)std::min(step, pl.max_splits - a.split0) * pairs;
+        if (pl.tiles == 1) walk(std::integral_constant<int, 1>{});
+        else if (pl.tiles == 2) walk(std::integral_constant<int, 2>{});
+        else if (pl.tiles == 3) walk(std::integral_constant<int, 3>{});
+        else walk(std::integral_constant<int, f32_max_tiles(D)>{});
+    }
     const int64_t items = (int64_t)total_q * a.hq;
     if (items > 0) {
         dim3 cgrid((unsigned)((items + kAttnWaves - 1) / kAttnWaves));
-        hipLaunchKernelGGL((attn_combine<T, D>), cgrid, dim3(kAttnThreads), 0, stream, a, total_q);
+        hipLaunchKernelGGL((attn_combine<D>), cgrid, dim3(kAttnThreads), 0, stream, a, total_q);
     }
 }
 
@@ -1880,11 +1985,12 @@ int attention_call(const verify_attn_params* params, int32_t total_q, int32_t ma
     a.split_blocks = pl.split_blocks;
     a.max_splits = pl.max_splits;
     a.row_groups = pl.row_groups;
+    a.rows_per_group = pl.tiles * 16;
     a.sinks = sinks;
     a.k_new = k_new;
     a.v_new = v_new;
-    if (p.head_dim == 128) launch_valu<float, 128>(a, pl, total_q, stream);
-    else launch_valu<float, 64>(a, pl, total_q, stream);
+    if (p.head_dim == 128) launch_f32<128>(a, pl, total_q, stream);
+    else launch_f32<64>(a, pl, total_q, stream);
     return check_launch();
 }
 
@@ -1938,7 +2044,7 @@ extern "C" int verify_attention_plan(const verify_attn_params* params, int32_t t
     } else {
         info[0] = 0;
         info[1] = pl.max_splits;
-        info[2] = kValuRows;
+        info[2] = pl.tiles * 16;
         info[3] = pl.row_groups;
         info[4] = pl.split_blocks;
     }
