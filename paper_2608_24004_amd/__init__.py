@@ -183,39 +183,62 @@ def _expect(t, name, shape=None, dtype=None, device=None):
         raise ValueError("%s is on %s, the call runs on %s" % (name, t.device, device))
 
 
-def _check_attention_tensors(q, k_cache, v_cache, block_tables, seq_lens=None, q_start=None,
-                             sinks=None, out=None, workspace=None):
+def _arg(t, name, shape, dtype, idx, device):
+    """Device address of a required caller tensor, checked by _expect and
+    _dev_ptr.  The tests that a good tensor passes are made here first, in one
+    go: with some ten tensors per call the full checks took as long as the
+    kernels of a small call (one request's attention: 21 us on the host, 14 us
+    on the GPU)."""
+    if (t is not None and t.dtype is dtype and t.get_device() == idx >= 0 and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return t.data_ptr()
+    _expect(t, name, shape, dtype, device)
+    # a call on tensors in host memory is refused by its first tensor, once
+    # all are checked
+    return _dev_ptr(t, name, dtype) if idx >= 0 else None
+
+
+def _workspace_arg(workspace, idx, device):
+    """Address and bytes of a caller's workspace."""
+    if workspace is None:
+        return None, 0
+    return (_arg(workspace, "workspace", None, workspace.dtype, idx, device),
+            workspace.numel() * workspace.element_size())
+
+
+def _layer_args(Hq, D, dtype, esize, idx, dev, k_cache, v_cache, block_tables, seq_lens, q_start):
+    """Addresses of a layer's cache and batch descriptor, and its AttnParams
+    (sliding_window, scale and kv_split_blocks 0)."""
     import torch
-    if q.dim() != 3:
-        raise ValueError("q must be [T, Hq, D], got %s" % (tuple(q.shape),))
-    T, Hq, D = q.shape
+    i32 = torch.int32
     if k_cache.dim() != 5:
         raise ValueError("k_cache must be [num_blocks, Hkv, D/x, 16, x], got %s" % (tuple(k_cache.shape),))
     nb, hkv = k_cache.shape[0], k_cache.shape[1]
-    x = 16 // q.element_size()
-    dev, i32 = q.device, torch.int32
-    _expect(k_cache, "k_cache", (nb, hkv, D // x, 16, x), q.dtype, dev)
-    _expect(v_cache, "v_cache", (nb, hkv, D, 16), q.dtype, dev)
+    x = 16 // esize
+    ptrs = [_arg(k_cache, "k_cache", (nb, hkv, D // x, 16, x), dtype, idx, dev),
+            _arg(v_cache, "v_cache", (nb, hkv, D, 16), dtype, idx, dev)]
     if block_tables.dim() != 2:
         raise ValueError("block_tables must be [B, max_blocks], got %s" % (tuple(block_tables.shape),))
-    B = block_tables.shape[0]
-    _expect(block_tables, "block_tables", None, i32, dev)
-    if seq_lens is not None:
-        _expect(seq_lens, "seq_lens", (B,), i32, dev)
-    if q_start is not None:
-        _expect(q_start, "q_start", (B + 1,), i32, dev)
-    if sinks is not None:
-        _expect(sinks, "sinks", (Hq,), torch.float32, dev)
-    if out is not None:
-        _expect(out, "out", tuple(q.shape), q.dtype, dev)
-    if workspace is not None:
-        _expect(workspace, "workspace", None, None, dev)
+    B, max_blocks = block_tables.shape
+    ptrs += [_arg(block_tables, "block_tables", None, i32, idx, dev),
+             _arg(seq_lens, "seq_lens", (B,), i32, idx, dev),
+             _arg(q_start, "q_start", (B + 1,), i32, idx, dev)]
+    return ptrs, AttnParams(B, Hq, hkv, D, 16, max_blocks, nb, 0, 0.0, _dtype_code(k_cache), 0)
+
+
+# torch.cuda.current_stream builds a Stream object per call (2 us)
+_raw_stream = None
 
 
 def _stream_ptr(stream, device):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ctypes.c_void_p(s.cuda_stream)
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda idx: torch.cuda.current_stream(idx).cuda_stream)
+    return _raw_stream(device.index)
 
 
 def _attn_params(q, k_cache, block_tables, sliding_window, scale, kv_split_blocks):
@@ -335,30 +358,57 @@ def verify_attention(q, k_cache, v_cache, block_tables, seq_lens, q_start, *, ma
     validate the descriptor on the device first (check_batch; raises
     BatchError, waits for the stream).
     """
+    return _attention_call("verify_attention", q, None, k_cache, v_cache, block_tables, seq_lens, q_start,
+                           max_q_len, max_seq_len, sliding_window, scale, kv_split_blocks, sinks, out,
+                           workspace, stream, check)
+
+
+def _attention_call(where, q, new, k_cache, v_cache, block_tables, seq_lens, q_start, max_q_len,
+                    max_seq_len, sliding_window, scale, kv_split_blocks, sinks, out, workspace, stream,
+                    check):
+    """verify_attention, and with new = (k_new, v_new) verify_attention_append."""
     import torch
-    _check_attention_tensors(q, k_cache, v_cache, block_tables, seq_lens, q_start, sinks, out,
-                             workspace)
-    _checked(check, "verify_attention", q_start=q_start, total_q=q.shape[0], max_q_len=max_q_len,
-             seq_lens=seq_lens, block_tables=block_tables, num_blocks=k_cache.shape[0],
-             max_seq_len=max_seq_len, sliding_window=sliding_window, stream=stream)
-    params = _attn_params(q, k_cache, block_tables, sliding_window, scale, kv_split_blocks)
+    if q.dim() != 3:
+        raise ValueError("q must be [T, Hq, D], got %s" % (tuple(q.shape),))
+    T, Hq, D = q.shape
+    dtype, dev = q.dtype, q.device
+    idx = dev.index if dev.type == "cuda" else -1
+    p_q = _arg(q, "q", None, dtype, idx, dev)
+    layer, params = _layer_args(Hq, D, dtype, q.element_size(), idx, dev, k_cache, v_cache, block_tables,
+                                seq_lens, q_start)
+    p_sinks = None if sinks is None else _arg(sinks, "sinks", (Hq,), torch.float32, idx, dev)
+    p_out = None if out is None else _arg(out, "out", (T, Hq, D), dtype, idx, dev)
+    p_ws, ws_have = _workspace_arg(workspace, idx, dev)
+    p_new = []
+    if new is not None:
+        shape = (T, k_cache.shape[1], D)
+        p_new = [_arg(new[0], "k_new", shape, dtype, idx, dev), _arg(new[1], "v_new", shape, dtype, idx, dev)]
+    if check or check is None and CHECK_BY_DEFAULT:
+        _checked(check, where, q_start=q_start, total_q=T, max_q_len=max_q_len, seq_lens=seq_lens,
+                 block_tables=block_tables, num_blocks=k_cache.shape[0], max_seq_len=max_seq_len,
+                 sliding_window=sliding_window, stream=stream)
+    params.sliding_window = int(sliding_window)
+    params.scale = float(scale)
+    params.kv_split_blocks = int(kv_split_blocks)
     if out is None:
         out = torch.empty_like(q)
-    ws_bytes = attention_workspace_size(q, k_cache, block_tables, max_q_len=max_q_len,
-                                        max_seq_len=max_seq_len, sliding_window=sliding_window,
-                                        scale=scale, kv_split_blocks=kv_split_blocks)
-    if workspace is None and ws_bytes > 0:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
-    ws_have = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    i32 = torch.int32
-    rc = library().verify_attention(
-        ctypes.byref(params), q.shape[0], int(max_q_len), int(max_seq_len),
-        _dev_ptr(q, "q"), _dev_ptr(k_cache, "k_cache", q.dtype), _dev_ptr(v_cache, "v_cache", q.dtype),
-        _dev_ptr(block_tables, "block_tables", i32), _dev_ptr(seq_lens, "seq_lens", i32),
-        _dev_ptr(q_start, "q_start", i32), _dev_ptr(sinks, "sinks", torch.float32),
-        _dev_ptr(out, "out", q.dtype), _dev_ptr(workspace, "workspace"), ws_have,
-        _stream_ptr(stream, q.device))
-    _check(rc, "verify_attention")
+        p_out = out.data_ptr()
+    size = dict(max_q_len=max_q_len, max_seq_len=max_seq_len, sliding_window=sliding_window, scale=scale,
+                kv_split_blocks=kv_split_blocks)
+    if workspace is None:
+        ws_have = attention_workspace_size(q, k_cache, block_tables, **size)
+        if ws_have > 0:
+            workspace = torch.empty(ws_have, dtype=torch.uint8, device=dev)
+            p_ws = workspace.data_ptr()
+    if idx < 0:
+        _dev_ptr(q, "q")
+    lib = library()
+    call = lib.verify_attention if new is None else lib.verify_attention_append
+    rc = call(ctypes.byref(params), T, int(max_q_len), int(max_seq_len), p_q, *p_new, *layer, p_sinks, p_out,
+              p_ws, ws_have, _stream_ptr(stream, dev))
+    if rc != OK:
+        attention_workspace_size(q, k_cache, block_tables, **size)  # what it refuses is its error
+        _check(rc, where)
     return out
 
 
@@ -370,36 +420,9 @@ def verify_attention_append(q, k_new, v_new, k_cache, v_cache, block_tables, seq
     tokens' K/V (k_new, v_new [T, Hkv, D], the cache's dtype) are stored into
     k_cache / v_cache in place while the attention reads them from k_new /
     v_new.  Same arguments and result as verify_attention; returns `out`."""
-    import torch
-    _check_attention_tensors(q, k_cache, v_cache, block_tables, seq_lens, q_start, sinks, out,
-                             workspace)
-    shape = (q.shape[0], k_cache.shape[1], q.shape[2])
-    _expect(k_new, "k_new", shape, q.dtype, q.device)
-    _expect(v_new, "v_new", shape, q.dtype, q.device)
-    _checked(check, "verify_attention_append", q_start=q_start, total_q=q.shape[0],
-             max_q_len=max_q_len, seq_lens=seq_lens, block_tables=block_tables,
-             num_blocks=k_cache.shape[0], max_seq_len=max_seq_len, sliding_window=sliding_window,
-             stream=stream)
-    params = _attn_params(q, k_cache, block_tables, sliding_window, scale, kv_split_blocks)
-    if out is None:
-        out = torch.empty_like(q)
-    ws_bytes = attention_workspace_size(q, k_cache, block_tables, max_q_len=max_q_len,
-                                        max_seq_len=max_seq_len, sliding_window=sliding_window,
-                                        scale=scale, kv_split_blocks=kv_split_blocks)
-    if workspace is None and ws_bytes > 0:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
-    ws_have = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    i32 = torch.int32
-    rc = library().verify_attention_append(
-        ctypes.byref(params), q.shape[0], int(max_q_len), int(max_seq_len), _dev_ptr(q, "q"),
-        _dev_ptr(k_new, "k_new", q.dtype), _dev_ptr(v_new, "v_new", q.dtype),
-        _dev_ptr(k_cache, "k_cache", q.dtype), _dev_ptr(v_cache, "v_cache", q.dtype),
-        _dev_ptr(block_tables, "block_tables", i32), _dev_ptr(seq_lens, "seq_lens", i32),
-        _dev_ptr(q_start, "q_start", i32), _dev_ptr(sinks, "sinks", torch.float32),
-        _dev_ptr(out, "out", q.dtype), _dev_ptr(workspace, "workspace"), ws_have,
-        _stream_ptr(stream, q.device))
-    _check(rc, "verify_attention_append")
-    return out
+    return _attention_call("verify_attention_append", q, (k_new, v_new), k_cache, v_cache, block_tables,
+                           seq_lens, q_start, max_q_len, max_seq_len, sliding_window, scale, kv_split_blocks,
+                           sinks, out, workspace, stream, check)
 
 
 def accept_workspace_size(num_seqs: int, total_q: int, vocab: int, dtype_code: int) -> int:
@@ -410,38 +433,60 @@ def accept_workspace_size(num_seqs: int, total_q: int, vocab: int, dtype_code: i
     return int(n.value)
 
 
-def _accept_buffers(logits, q_start, argmax_out, accept_len, num_emitted, emitted, workspace,
-                    need_workspace=True):
+def _accept_outputs(T, q_start, argmax_out, accept_len, num_emitted, emitted, idx, dev):
+    """Batch size, then the acceptance outputs (allocated where not given) and
+    the addresses of q_start and of them."""
     import torch
-    if logits.dim() != 2:
-        raise ValueError("logits must be [T, V], got %s" % (tuple(logits.shape),))
-    T, V = logits.shape
+    i32 = torch.int32
     if q_start.dim() != 1 or q_start.shape[0] < 1:
         raise ValueError("q_start must be [B + 1], got %s" % (tuple(q_start.shape),))
     B = q_start.shape[0] - 1
-    dev = logits.device
-    i32 = torch.int32
-    _expect(q_start, "q_start", None, i32, dev)
+    p_qs = _arg(q_start, "q_start", None, i32, idx, dev)
+    outs, ptrs = [], []
     for name, t, n in (("argmax_out", argmax_out, T), ("accept_len", accept_len, B),
                        ("num_emitted", num_emitted, B), ("emitted", emitted, T)):
-        if t is not None:
-            _expect(t, name, (n,), i32, dev)
-    if workspace is not None:
-        _expect(workspace, "workspace", None, None, dev)
+        if t is None:
+            t = torch.empty(n, dtype=i32, device=dev)
+            ptrs.append(t.data_ptr())
+        else:
+            ptrs.append(_arg(t, name, (n,), i32, idx, dev))
+        outs.append(t)
+    return B, p_qs, outs, ptrs
+
+
+def _accept_call(where, logits, tokens, q_start, outs, workspace, stream, check, draw=(), noalloc=False):
+    """verify_accept, verify_accept_noalloc (noalloc) and verify_accept_sampled
+    (draw = (temperature, seed, offset)); outs = (argmax or draw, accept_len,
+    num_emitted, emitted), None where they are to be allocated."""
+    import torch
+    i32 = torch.int32
+    if logits.dim() != 2:
+        raise ValueError("logits must be [T, V], got %s" % (tuple(logits.shape),))
+    T, V = logits.shape
+    dev = logits.device
+    idx = dev.index if dev.type == "cuda" else -1
+    p_logits = _arg(logits, "logits", None, logits.dtype, idx, dev)
+    B, p_qs, outs, (p_am, p_acc, p_num, p_em) = _accept_outputs(T, q_start, *outs, idx, dev)
+    p_ws, ws_have = _workspace_arg(workspace, idx, dev)
     code = _dtype_code(logits)
-    if argmax_out is None:
-        argmax_out = torch.empty(T, dtype=i32, device=dev)
-    if accept_len is None:
-        accept_len = torch.empty(B, dtype=i32, device=dev)
-    if num_emitted is None:
-        num_emitted = torch.empty(B, dtype=i32, device=dev)
-    if emitted is None:
-        emitted = torch.empty(T, dtype=i32, device=dev)
-    ws_bytes = accept_workspace_size(B, T, V, code) if need_workspace else 0
-    if workspace is None and ws_bytes > 0:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    ws_have = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    return B, T, V, code, argmax_out, accept_len, num_emitted, emitted, workspace, ws_have
+    if workspace is None and not noalloc:
+        ws_have = accept_workspace_size(B, T, V, code)
+        if ws_have > 0:
+            workspace = torch.empty(ws_have, dtype=torch.uint8, device=dev)
+            p_ws = workspace.data_ptr()
+    p_tok = _arg(tokens, "tokens", (T,), i32, idx, dev)
+    if check or check is None and CHECK_BY_DEFAULT:
+        _checked(check, where, q_start=q_start, total_q=T, stream=stream)
+    if idx < 0:
+        _dev_ptr(logits, "logits")
+    ws = () if noalloc else (p_ws, ws_have)
+    rc = getattr(library(), where)(B, T, V, V, code, p_logits, p_tok, p_qs, *draw, p_am, p_acc, p_num, p_em, *ws,
+                                   _stream_ptr(stream, dev))
+    if rc != OK:
+        if not noalloc:
+            accept_workspace_size(B, T, V, code)  # what it refuses is its error
+        _check(rc, where)
+    return outs[1], outs[2], outs[3], outs[0]
 
 
 def verify_accept(logits, tokens, q_start, *, argmax_out=None, accept_len=None, num_emitted=None,
@@ -452,20 +497,8 @@ def verify_accept(logits, tokens, q_start, *, argmax_out=None, accept_len=None, 
     device.  Returns (accept_len [B], num_emitted [B], emitted [T], argmax [T]).
     check: validate q_start on the device first (check_batch).
     """
-    import torch
-    i32 = torch.int32
-    B, T, V, code, argmax_out, accept_len, num_emitted, emitted, workspace, ws_have = \
-        _accept_buffers(logits, q_start, argmax_out, accept_len, num_emitted, emitted, workspace)
-    _expect(tokens, "tokens", (T,), i32, logits.device)
-    _checked(check, "verify_accept", q_start=q_start, total_q=T, stream=stream)
-    rc = library().verify_accept(
-        B, T, V, V, code, _dev_ptr(logits, "logits"), _dev_ptr(tokens, "tokens", i32),
-        _dev_ptr(q_start, "q_start", i32), _dev_ptr(argmax_out, "argmax_out", i32),
-        _dev_ptr(accept_len, "accept_len", i32), _dev_ptr(num_emitted, "num_emitted", i32),
-        _dev_ptr(emitted, "emitted", i32), _dev_ptr(workspace, "workspace"), ws_have,
-        _stream_ptr(stream, logits.device))
-    _check(rc, "verify_accept")
-    return accept_len, num_emitted, emitted, argmax_out
+    return _accept_call("verify_accept", logits, tokens, q_start, (argmax_out, accept_len, num_emitted, emitted),
+                        workspace, stream, check)
 
 
 def verify_accept_noalloc(logits, tokens, q_start, *, argmax_out=None, accept_len=None,
@@ -475,20 +508,8 @@ def verify_accept_noalloc(logits, tokens, q_start, *, argmax_out=None, accept_le
     overlap on one GPU race).  Outputs not passed in are allocated here, by
     torch, before the call; the C call allocates nothing.  Returns
     (accept_len [B], num_emitted [B], emitted [T], argmax [T])."""
-    import torch
-    i32 = torch.int32
-    B, T, V, code, argmax_out, accept_len, num_emitted, emitted, _, _ = \
-        _accept_buffers(logits, q_start, argmax_out, accept_len, num_emitted, emitted, None,
-                        need_workspace=False)
-    _expect(tokens, "tokens", (T,), i32, logits.device)
-    _checked(check, "verify_accept_noalloc", q_start=q_start, total_q=T, stream=stream)
-    rc = library().verify_accept_noalloc(
-        B, T, V, V, code, _dev_ptr(logits, "logits"), _dev_ptr(tokens, "tokens", i32),
-        _dev_ptr(q_start, "q_start", i32), _dev_ptr(argmax_out, "argmax_out", i32),
-        _dev_ptr(accept_len, "accept_len", i32), _dev_ptr(num_emitted, "num_emitted", i32),
-        _dev_ptr(emitted, "emitted", i32), _stream_ptr(stream, logits.device))
-    _check(rc, "verify_accept_noalloc")
-    return accept_len, num_emitted, emitted, argmax_out
+    return _accept_call("verify_accept_noalloc", logits, tokens, q_start,
+                        (argmax_out, accept_len, num_emitted, emitted), None, stream, check, noalloc=True)
 
 
 def verify_accept_sampled(logits, tokens, q_start, *, temperature: float, seed: int, offset: int = 0,
@@ -502,22 +523,11 @@ def verify_accept_sampled(logits, tokens, q_start, *, temperature: float, seed: 
     Same layouts as verify_accept.  Returns (accept_len [B], num_emitted [B],
     emitted [T], sampled [T]).
     """
-    import torch
-    i32 = torch.int32
     if not 0 <= int(seed) < (1 << 64) or not 0 <= int(offset) < (1 << 32):
         raise ValueError("seed must fit 64 bits and offset 32 bits, unsigned")
-    B, T, V, code, sampled_out, accept_len, num_emitted, emitted, workspace, ws_have = \
-        _accept_buffers(logits, q_start, sampled_out, accept_len, num_emitted, emitted, workspace)
-    _expect(tokens, "tokens", (T,), i32, logits.device)
-    _checked(check, "verify_accept_sampled", q_start=q_start, total_q=T, stream=stream)
-    rc = library().verify_accept_sampled(
-        B, T, V, V, code, _dev_ptr(logits, "logits"), _dev_ptr(tokens, "tokens", i32),
-        _dev_ptr(q_start, "q_start", i32), float(temperature), int(seed), int(offset),
-        _dev_ptr(sampled_out, "sampled_out", i32), _dev_ptr(accept_len, "accept_len", i32),
-        _dev_ptr(num_emitted, "num_emitted", i32), _dev_ptr(emitted, "emitted", i32),
-        _dev_ptr(workspace, "workspace"), ws_have, _stream_ptr(stream, logits.device))
-    _check(rc, "verify_accept_sampled")
-    return accept_len, num_emitted, emitted, sampled_out
+    return _accept_call("verify_accept_sampled", logits, tokens, q_start,
+                        (sampled_out, accept_len, num_emitted, emitted), workspace, stream, check,
+                        draw=(float(temperature), int(seed), int(offset)))
 
 
 def lmhead_accept_workspace_size(num_seqs: int, total_q: int, hidden_size: int, vocab: int,
@@ -547,41 +557,30 @@ def verify_lmhead_accept(hidden, weight, tokens, q_start, *, argmax_out=None, ac
     V, H2 = weight.shape
     if H != H2:
         raise ValueError("hidden sizes differ: %d vs %d" % (H, H2))
-    if q_start.dim() != 1 or q_start.shape[0] < 1:
-        raise ValueError("q_start must be [B + 1], got %s" % (tuple(q_start.shape),))
-    B = q_start.shape[0] - 1
-    dev = hidden.device
-    _expect(weight, "weight", None, hidden.dtype, dev)
-    _expect(tokens, "tokens", (T,), i32, dev)
-    _expect(q_start, "q_start", None, i32, dev)
-    for name, t, n in (("argmax_out", argmax_out, T), ("accept_len", accept_len, B),
-                       ("num_emitted", num_emitted, B), ("emitted", emitted, T)):
-        if t is not None:
-            _expect(t, name, (n,), i32, dev)
-    if workspace is not None:
-        _expect(workspace, "workspace", None, None, dev)
-    _checked(check, "verify_lmhead_accept", q_start=q_start, total_q=T, stream=stream)
+    dev, dtype = hidden.device, hidden.dtype
+    idx = dev.index if dev.type == "cuda" else -1
+    p_h = _arg(hidden, "hidden", None, dtype, idx, dev)
+    p_w = _arg(weight, "weight", None, dtype, idx, dev)
+    p_tok = _arg(tokens, "tokens", (T,), i32, idx, dev)
+    B, p_qs, outs, (p_am, p_acc, p_num, p_em) = _accept_outputs(T, q_start, argmax_out, accept_len, num_emitted,
+                                                                emitted, idx, dev)
+    p_ws, ws_have = _workspace_arg(workspace, idx, dev)
+    if check or check is None and CHECK_BY_DEFAULT:
+        _checked(check, "verify_lmhead_accept", q_start=q_start, total_q=T, stream=stream)
     code = _dtype_code(hidden)
-    if argmax_out is None:
-        argmax_out = torch.empty(T, dtype=i32, device=dev)
-    if accept_len is None:
-        accept_len = torch.empty(B, dtype=i32, device=dev)
-    if num_emitted is None:
-        num_emitted = torch.empty(B, dtype=i32, device=dev)
-    if emitted is None:
-        emitted = torch.empty(T, dtype=i32, device=dev)
-    ws_bytes = lmhead_accept_workspace_size(B, T, H, V, code)
-    if workspace is None and ws_bytes > 0:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    ws_have = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = library().verify_lmhead_accept(
-        B, T, H, V, code, _dev_ptr(hidden, "hidden"), _dev_ptr(weight, "weight", hidden.dtype),
-        _dev_ptr(tokens, "tokens", i32), _dev_ptr(q_start, "q_start", i32),
-        _dev_ptr(argmax_out, "argmax_out", i32), _dev_ptr(accept_len, "accept_len", i32),
-        _dev_ptr(num_emitted, "num_emitted", i32), _dev_ptr(emitted, "emitted", i32),
-        _dev_ptr(workspace, "workspace"), ws_have, _stream_ptr(stream, dev))
-    _check(rc, "verify_lmhead_accept")
-    return accept_len, num_emitted, emitted, argmax_out
+    if workspace is None:
+        ws_have = lmhead_accept_workspace_size(B, T, H, V, code)
+        if ws_have > 0:
+            workspace = torch.empty(ws_have, dtype=torch.uint8, device=dev)
+            p_ws = workspace.data_ptr()
+    if idx < 0:
+        _dev_ptr(hidden, "hidden")
+    rc = library().verify_lmhead_accept(B, T, H, V, code, p_h, p_w, p_tok, p_qs, p_am, p_acc, p_num, p_em, p_ws,
+                                        ws_have, _stream_ptr(stream, dev))
+    if rc != OK:
+        lmhead_accept_workspace_size(B, T, H, V, code)  # what it refuses is its error
+        _check(rc, "verify_lmhead_accept")
+    return outs[1], outs[2], outs[3], outs[0]
 
 
 def verify_budget(cand_start, cand_len, cand_tokens, last_token, *, alpha: float, g_min: float,
@@ -601,36 +600,36 @@ def verify_budget(cand_start, cand_len, cand_tokens, last_token, *, alpha: float
     B = cand_start.shape[0] - 1
     C, max_len = cand_tokens.shape
     dev = cand_start.device
-    i32 = torch.int32
-    _expect(cand_len, "cand_len", (C,), i32, dev)
-    _expect(cand_tokens, "cand_tokens", None, i32, dev)
-    _expect(last_token, "last_token", (B,), i32, dev)
-    if ctx_len is not None:
-        _expect(ctx_len, "ctx_len", (B,), i32, dev)
+    idx = dev.index if dev.type == "cuda" else -1
+    i32, f64 = torch.int32, torch.float64
+    p_start = _arg(cand_start, "cand_start", None, i32, idx, dev)
+    p_len = _arg(cand_len, "cand_len", (C,), i32, idx, dev)
+    p_cand = _arg(cand_tokens, "cand_tokens", None, i32, idx, dev)
+    p_last = _arg(last_token, "last_token", (B,), i32, idx, dev)
+    p_ctx = None if ctx_len is None else _arg(ctx_len, "ctx_len", (B,), i32, idx, dev)
     o = dict(out or {})
-    shapes = dict(score=(B, torch.float64), agree=(B, i32), prefix_len=(B, i32), source=(B, i32),
-                  draft_len=(B, i32), q_start=(B + 1, i32), tokens=(B * (max_len + 1), i32))
+    shapes = [("score", B, f64), ("agree", B, i32), ("prefix_len", B, i32), ("source", B, i32),
+              ("draft_len", B, i32), ("q_start", B + 1, i32), ("tokens", B * (max_len + 1), i32)]
     if ctx_len is not None:
-        shapes["seq_lens"] = (B, i32)
-    for k, (n, dt) in shapes.items():
+        shapes.append(("seq_lens", B, i32))
+    ptrs = []
+    for k, n, dt in shapes:
         if k not in o:
-            o[k] = torch.empty(max(n, 1) if k == "tokens" else n, dtype=dt, device=dev)
+            o[k] = t = torch.empty(max(n, 1) if k == "tokens" else n, dtype=dt, device=dev)
+            ptrs.append(t.data_ptr())
         elif k == "tokens":
             # the capacity is passed to the call, which checks it
-            _expect(o[k], k, None, dt, dev)
+            ptrs.append(_arg(o[k], k, None, dt, idx, dev))
             if o[k].dim() != 1:
                 raise ValueError("tokens must be one-dimensional")
         else:
-            _expect(o[k], k, (n,), dt, dev)
-    rc = library().verify_budget(
-        B, C, max_len, _dev_ptr(cand_start, "cand_start", i32), _dev_ptr(cand_len, "cand_len", i32),
-        _dev_ptr(cand_tokens, "cand_tokens", i32), _dev_ptr(last_token, "last_token", i32),
-        _dev_ptr(ctx_len, "ctx_len", i32), float(alpha), float(g_min),
-        _dev_ptr(o["score"], "score", torch.float64), _dev_ptr(o["agree"], "agree", i32),
-        _dev_ptr(o["prefix_len"], "prefix_len", i32), _dev_ptr(o["source"], "source", i32),
-        _dev_ptr(o["draft_len"], "draft_len", i32), _dev_ptr(o["q_start"], "q_start", i32),
-        _dev_ptr(o["tokens"], "tokens", i32), o["tokens"].numel(),
-        _dev_ptr(o.get("seq_lens"), "seq_lens", i32), _stream_ptr(stream, dev))
+            ptrs.append(_arg(o[k], k, (n,), dt, idx, dev))
+    if ctx_len is None:
+        ptrs.append(_dev_ptr(o.get("seq_lens"), "seq_lens", i32))
+    if idx < 0:
+        _dev_ptr(cand_start, "cand_start")
+    rc = library().verify_budget(B, C, max_len, p_start, p_len, p_cand, p_last, p_ctx, float(alpha), float(g_min),
+                                 *ptrs[:7], o["tokens"].numel(), ptrs[7], _stream_ptr(stream, dev))
     _check(rc, "verify_budget")
     return o
 
@@ -647,19 +646,19 @@ def verify_kv_append(k_new, v_new, k_cache, v_cache, block_tables, seq_lens, q_s
     _expect(v_new, "v_new", tuple(k_new.shape), k_new.dtype, k_new.device)
     if q_start.dim() != 1 or q_start.shape[0] < 1:
         raise ValueError("q_start must be [B + 1], got %s" % (tuple(q_start.shape),))
-    probe = torch.empty((0, k_new.shape[1], k_new.shape[2]), dtype=k_new.dtype, device=k_new.device)
-    _check_attention_tensors(probe, k_cache, v_cache, block_tables, seq_lens, q_start)
-    if k_cache.shape[1] != k_new.shape[1]:
-        raise ValueError("k_new has %d KV heads, the cache %d" % (k_new.shape[1], k_cache.shape[1]))
-    params = _attn_params(probe, k_cache, block_tables, 0, 0.0, 0)
-    i32 = torch.int32
-    _checked(check, "verify_kv_append", q_start=q_start, total_q=k_new.shape[0], seq_lens=seq_lens,
-             block_tables=block_tables, num_blocks=k_cache.shape[0],
-             max_seq_len=16 * block_tables.shape[1], sliding_window=1, stream=stream)
-    rc = library().verify_kv_append(
-        ctypes.byref(params), k_new.shape[0], _dev_ptr(k_new, "k_new"),
-        _dev_ptr(v_new, "v_new", k_new.dtype), _dev_ptr(block_tables, "block_tables", i32),
-        _dev_ptr(seq_lens, "seq_lens", i32), _dev_ptr(q_start, "q_start", i32),
-        _dev_ptr(k_cache, "k_cache", k_new.dtype), _dev_ptr(v_cache, "v_cache", k_new.dtype),
-        _stream_ptr(stream, k_new.device))
+    T, hkv, D = k_new.shape
+    dtype, dev = k_new.dtype, k_new.device
+    idx = dev.index if dev.type == "cuda" else -1
+    p_k, p_v = _arg(k_new, "k_new", None, dtype, idx, dev), _arg(v_new, "v_new", None, dtype, idx, dev)
+    (p_kc, p_vc, *desc), params = _layer_args(hkv, D, dtype, k_new.element_size(), idx, dev, k_cache, v_cache,
+                                              block_tables, seq_lens, q_start)
+    if k_cache.shape[1] != hkv:
+        raise ValueError("k_new has %d KV heads, the cache %d" % (hkv, k_cache.shape[1]))
+    if check or check is None and CHECK_BY_DEFAULT:
+        _checked(check, "verify_kv_append", q_start=q_start, total_q=T, seq_lens=seq_lens,
+                 block_tables=block_tables, num_blocks=k_cache.shape[0],
+                 max_seq_len=16 * block_tables.shape[1], sliding_window=1, stream=stream)
+    if idx < 0:
+        _dev_ptr(k_new, "k_new")
+    rc = library().verify_kv_append(ctypes.byref(params), T, p_k, p_v, *desc, p_kc, p_vc, _stream_ptr(stream, dev))
     _check(rc, "verify_kv_append")
