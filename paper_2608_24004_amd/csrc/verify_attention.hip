@@ -1463,12 +1463,19 @@ __global__ __launch_bounds__(kAttnThreads) void attn_combine(AttnArgs a, int tot
 // transposed ([D][16]).  One workgroup per (request, KV head) writes all of
 // the request's new tokens of that head, so the tokens that share a 32-byte
 // V sector (consecutive slots of one dimension) are written by one compute
-// unit and leave its L2 as one sector.  K moves in 16-byte chunks, thread
-// items ordered (chunk, token) so that consecutive threads write consecutive
-// slots; V moves element by element, items ordered (dimension, token).
-// Tokens with a negative position or a block id outside [0, num_blocks) are
-// skipped.
+// unit and leave its L2 as one sector.  Tokens with a negative position or a
+// block id outside [0, num_blocks) are skipped.
+//
+// The call is a chain of memory latencies (its bytes take under a microsecond),
+// so each is paid once: kAppendTokens tokens at a time, the rows are read whole
+// into LDS (16 bytes per thread, rows contiguous) beside the block ids, and
+// leave it transposed, thread items ordered so that consecutive threads write
+// consecutive slots: K in 16-byte chunks, V element by element.  Read by
+// element in the order of the writes, with the block id looked up for each, the
+// loop over dimensions paid the latency over and over (64 requests of 1 to 17
+// tokens, 8 heads of 128: 9.7 -> 6.5 us).
 constexpr int kAppendThreads = 256;
+constexpr int kAppendTokens = 32;
 
 template <typename T, int D>
 __global__ __launch_bounds__(kAppendThreads) void attn_kv_append(
@@ -1478,33 +1485,59 @@ __global__ __launch_bounds__(kAppendThreads) void attn_kv_append(
     T* __restrict__ vc) {
     constexpr int X = Storage<T>::kPer16B;
     constexpr int NC = D / X;  // 16-byte chunks per key
-    const int i = blockIdx.x, g = blockIdx.y;
+    // rows of NC chunks, one more per row so that the reads down a column of
+    // consecutive tokens spread over the banks
+    __shared__ uint4 ks[kAppendTokens][NC + 1], vs[kAppendTokens][NC + 1];
+    __shared__ int32_t blk[kAppendTokens];
+    const int i = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
     const int q0 = q_start[i];
     const int n = q_start[i + 1] - q0;
     if (n <= 0) return;
     const int64_t p0 = (int64_t)seq_lens[i] - n;  // position of the request's row 0
     const int32_t* bt = block_tables + (int64_t)i * max_blocks;
-    // physical block of token j, or -1 when the token is skipped
-    auto block_of = [&](int j) {
-        const int64_t p = p0 + j;
-        if (p < 0 || p / kBlockTokens >= max_blocks) return -1;
-        const int b = bt[p / kBlockTokens];
-        return (b < 0 || b >= num_blocks) ? -1 : b;
-    };
-    for (int it = threadIdx.x; it < n * NC; it += kAppendThreads) {
-        const int c = it / n, j = it - c * n;
-        const int b = block_of(j);
-        if (b < 0) continue;
-        const int t = (int)((p0 + j) % kBlockTokens);
-        const uint4 v = ld16(k_new + ((int64_t)(q0 + j) * hkv + g) * D + c * X);
-        *reinterpret_cast<uint4*>(kc + ((((int64_t)b * hkv + g) * NC + c) * kBlockTokens + t) * X) = v;
-    }
-    for (int it = threadIdx.x; it < n * D; it += kAppendThreads) {
-        const int d = it / n, j = it - d * n;
-        const int b = block_of(j);
-        if (b < 0) continue;
-        const int t = (int)((p0 + j) % kBlockTokens);
-        vc[(((int64_t)b * hkv + g) * D + d) * kBlockTokens + t] = v_new[((int64_t)(q0 + j) * hkv + g) * D + d];
+    // rows that a caller aligned to their elements only are read by element
+    const bool wide = (((uintptr_t)k_new | (uintptr_t)v_new) & 15) == 0;
+    for (int j0 = 0; j0 < n; j0 += kAppendTokens) {
+        const int m = min(kAppendTokens, n - j0);
+        if (j0 > 0) __syncthreads();
+        const T* kr = k_new + ((int64_t)(q0 + j0) * hkv + g) * D;
+        const T* vr = v_new + ((int64_t)(q0 + j0) * hkv + g) * D;
+        const int64_t stride = (int64_t)hkv * D;
+        if (wide) {
+#pragma unroll
+            for (int u = 0; u < kAppendTokens * NC / kAppendThreads; ++u) {
+                const int it = u * kAppendThreads + tid, j = it / NC, c = it % NC;
+                if (j < m) {
+                    ks[j][c] = ld16(kr + j * stride + c * X);
+                    vs[j][c] = ld16(vr + j * stride + c * X);
+                }
+            }
+        } else {
+            for (int it = tid; it < m * D; it += kAppendThreads) {
+                const int j = it / D, d = it % D;
+                reinterpret_cast<T*>(ks[j])[d] = kr[j * stride + d];
+                reinterpret_cast<T*>(vs[j])[d] = vr[j * stride + d];
+            }
+        }
+        if (tid < m) {
+            const int64_t p = p0 + j0 + tid;
+            int b = -1;
+            if (p >= 0 && p / kBlockTokens < max_blocks) b = bt[p / kBlockTokens];
+            blk[tid] = b >= 0 && b < num_blocks ? b : -1;
+        }
+        __syncthreads();
+        // tokens fastest, over the next power of two of them
+        const int sh = m > 1 ? 32 - __clz(m - 1) : 0;
+        const int j = tid & ((1 << sh) - 1), step = kAppendThreads >> sh;
+        const int b = j < m ? blk[j] : -1;
+        if (b >= 0) {
+            const int t = (int)((p0 + j0 + j) % kBlockTokens);
+            const int64_t tile = ((int64_t)b * hkv + g) * D * kBlockTokens;
+            for (int c = tid >> sh; c < NC; c += step)
+                *reinterpret_cast<uint4*>(kc + tile + (c * kBlockTokens + t) * X) = ks[j][c];
+            for (int d = tid >> sh; d < D; d += step)
+                vc[tile + d * kBlockTokens + t] = reinterpret_cast<const T*>(vs[j])[d];
+        }
     }
 }
 
