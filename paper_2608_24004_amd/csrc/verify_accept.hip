@@ -181,13 +181,23 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_chunks(
 // below a score already reached in the chunk can be neither the row's maximum
 // nor tied with it.  The others are queued per wavefront in LDS and evaluated
 // 64 at a time, one per lane, so the logs run on full wavefronts.  The
-// threshold is the wavefront's best evaluated score, raised after every
-// batch; after the first batches almost no logit is queued.
+// threshold starts at the best score of the workgroup's most promising first
+// logits and is raised to the wavefront's best after every batch.  Arithmetic
+// bounds it (384 rows of 128256 bf16 logits: 2.5e7 vector instructions, the
+// 64-bit products among them no slower than the rest), so instructions are what
+// it saves: one three-way xor per generator word, one test for the four logits of
+// a block, one ballot for a vector's blocks; with the call's scan 54.9 -> 46 us.
 struct SampleParams {
     uint32_t k0, k1;   // seed: key words
     uint32_t offset;   // counter word 2 (e.g. the decoding step)
     float inv_t;       // 1 / T, rounded to fp32 on the host
 };
+
+// a ^ b ^ c as one v_bitop3_b32 (truth table 0xf0 ^ 0xcc ^ 0xaa); the compiler
+// writes two v_xor_b32, 16 instructions more per generator block.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
 
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t out[4]) {
@@ -200,8 +210,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
         // one 32 x 32 -> 64-bit product gives both halves of each multiply
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
         c0 = n0;
         c1 = (uint32_t)p1;
         c2 = n2;
@@ -258,6 +268,7 @@ __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
     constexpr int E = Storage<T>::kPer16B;
     // queued logit: (x bits, code k, index, unused)
     __shared__ uint4 queue[kArgmaxThreads / kWave][kSampleQueue];
+    __shared__ float first[kArgmaxThreads / kWave];  // the wavefronts' first thresholds
     __shared__ uint64_t red[kArgmaxThreads / kWave];
     const int64_t row = row0 + blockIdx.y;
     const uint32_t urow = (uint32_t)row;
@@ -298,13 +309,41 @@ __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
         const float wm = wave_max_xor(best, kWave);
         thr = fmaxf(thr, __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wm))));
     };
+    // Evaluates each lane's most promising logit of the wavefront's first vector
+    // (the highest bound), so that the scan starts with a threshold near the
+    // best of the workgroup's first 256 E logits.  From -inf the queue filled
+    // with whatever came first, and a wavefront's share of a chunk (some 50
+    // logits per lane) was over before the threshold had risen.
+    auto prime = [&](const uint4& v, uint32_t base, bool have) {
+        float x[E];
+        unpack16(v, x, T());
+        const bool live = have && !((E == 8) ? any_nan_bf16x8(v) : any_nan_f32x4(v));
+        float ub = -INFINITY, px = 0.f;
+        uint32_t pk = 0, pidx = kNone;
+#pragma unroll
+        for (int b = 0; b < E / 4; ++b) {
+            uint32_t w[4];
+            philox4x32_10((base >> 2) + b, urow, sp.offset, 0u, sp.k0, sp.k1, w);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float u = fmaf(x[4 * b + e], sp.inv_t, gumbel_bound(w[e] >> 9));
+                const bool up = u > ub;
+                ub = up ? u : ub;
+                px = up ? x[4 * b + e] : px;
+                pk = up ? w[e] >> 9 : pk;
+                pidx = up ? base + 4 * b + e : pidx;
+            }
+        }
+        if (live && pidx != kNone) take(px, pk, pidx);
+        thr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wave_max_xor(best, kWave))));
+    };
     // One 16-byte vector of E logits at element `base`; `have` is false for
     // lanes past the chunk's last vector, which still take part in the ballots.
     auto scan = [&](const uint4& v, uint32_t base, bool have) {
         float x[E];
         unpack16(v, x, T());
         const bool nan = have && ((E == 8) ? any_nan_bf16x8(v) : any_nan_f32x4(v));
-        if (nan && nan_idx == kNone) {
+        if (__ballot(nan) != 0 && nan && nan_idx == kNone) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 if (x[e] != x[e]) { nan_idx = base + e; break; }
@@ -312,18 +351,34 @@ __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
         }
         // a lane that holds a NaN reports it; its other logits drop out
         const bool live = have && nan_idx == kNone;
+        float xm[E / 4];
+        bool any = false;
 #pragma unroll
         for (int b = 0; b < E / 4; ++b) {
-            const float xm = fmaxf(fmaxf(x[4 * b], x[4 * b + 1]), fmaxf(x[4 * b + 2], x[4 * b + 3]));
-            const bool any = live && fmaf(xm, sp.inv_t, kGumbelMax) >= thr;
-            if (__ballot(any) == 0) continue;
-            uint32_t w[4];
-            philox4x32_10((base >> 2) + b, urow, sp.offset, 0u, sp.k0, sp.k1, w);
+            xm[b] = fmaxf(fmaxf(x[4 * b], x[4 * b + 1]), fmaxf(x[4 * b + 2], x[4 * b + 3]));
+            any |= fmaf(xm[b], sp.inv_t, kGumbelMax) >= thr;
+        }
+        if (__ballot(live && any) == 0) return;
+        uint32_t w[E / 4][4];
+        bool may[E / 4], some = false;
+#pragma unroll
+        for (int b = 0; b < E / 4; ++b) {
+            philox4x32_10((base >> 2) + b, urow, sp.offset, 0u, sp.k0, sp.k1, w[b]);
+            // the bound rises with the code and the score with both, so the
+            // largest logit under the largest code's bound covers the block's four
+            const uint32_t wmax = max(max(w[b][0], w[b][1]), max(w[b][2], w[b][3]));
+            may[b] = live && fmaf(xm[b], sp.inv_t, gumbel_bound(wmax >> 9)) >= thr;
+            some |= may[b];
+        }
+        if (__ballot(some) == 0) return;
+#pragma unroll
+        for (int b = 0; b < E / 4; ++b) {
+            if (__ballot(may[b]) == 0) continue;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const uint32_t k = w[e] >> 9;
+                const uint32_t k = w[b][e] >> 9;
                 const float xe = x[4 * b + e];
-                const bool cand = any && fmaf(xe, sp.inv_t, gumbel_bound(k)) >= thr;
+                const bool cand = may[b] && fmaf(xe, sp.inv_t, gumbel_bound(k)) >= thr;
                 const uint64_t bal = __ballot(cand);
                 if (bal == 0) continue;
                 if (cand) {
@@ -363,7 +418,15 @@ __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
                 dst[u] = vi < nvec ? ld16_stream(vp + vi) : make_uint4(0u, 0u, 0u, 0u);
             }
         };
-        if (wave_first < nvec) load(0, cur);
+        if (wave_first < nvec) {
+            load(0, cur);
+            prime(cur[0], (uint32_t)(lo + (int64_t)tid * E), tid < nvec);
+        }
+        if (lane == 0) first[wid] = thr;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kArgmaxThreads / kWave; ++w) thr = fmaxf(thr, first[w]);
+        thr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(thr)));
         for (int64_t v0 = 0; v0 + wave_first < nvec; v0 += kStep) {
             if (v0 + kStep + wave_first < nvec) load(v0 + kStep, nxt);
 #pragma unroll
