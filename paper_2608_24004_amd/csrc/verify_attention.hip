@@ -1601,10 +1601,13 @@ constexpr int kSlotsPerPair = 24;
 // compute units the walk is not longer than a share of the batch's: 256 pairs
 // of 32 / 63 blocks 16.5 / 31.4 against 23.3 / 37.6 us, 1024 pairs of 63
 // blocks 99 against 106 us (head dim 128) and 63 against 89 us (head dim 64).
-// In between the line rises with the pairs.  From 64 blocks on the
-// one-wavefront shapes take over, and a pair would be one wavefront's alone.
-bool whole_pairs(int64_t nb_max, int64_t pairs, int64_t cus) {
-    return nb_max <= std::min<int64_t>(63, 16 + 48 * pairs / cus);
+// From half a pair per compute unit on the line rises with the pairs (30 pairs
+// of 21 blocks and up to eight tiles lost 36.2 -> 38.6 us whole), to 127 blocks;
+// the several-tile one-wavefront shapes, which start at 64 blocks, stay below
+// that: a pair would be one wavefront's alone.
+bool whole_pairs(int64_t nb_max, int64_t pairs, int64_t cus, bool one_wave_many_tiles) {
+    if (nb_max > (one_wave_many_tiles ? 63 : 127)) return false;
+    return nb_max <= 16 + (2 * pairs >= cus ? 48 * pairs / cus : 0);
 }
 
 // LDS stages (blocks) of a workgroup's ring.  A step computes two of them while
@@ -1757,7 +1760,7 @@ int plan_class(const verify_attn_params* p, int64_t rows, int64_t nb_max, int ro
         c.nwg = (int)(resident * mult);
     }
     c.slots = pairs + c.nwg;
-    if (c.spb == 0 && whole_pairs(nb_max, pairs, device_cus())) {
+    if (c.spb == 0 && whole_pairs(nb_max, pairs, device_cus(), c.nw == 1 && c.tpw > 1)) {
         c.whole = true;
         c.nwg = (int)pairs;
         c.slots = 0;
@@ -1874,8 +1877,13 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
                                m.unit_start, m.slot_o, m.slot_lse, m.out);
         };
         if (pairs <= 0) return;
-        // more than a round of slots per pair: four thread groups share a row
-        if (a.nwg > kCombineSlots * pairs) combine(std::integral_constant<int, 4>{});
+        // more than a round of slots per pair: four thread groups share a row, if
+        // the four times larger grid is resident at once: 88 pairs of 52 rows 27.0 ->
+        // 23.3 us with it, but 41 pairs of 240 rows
+        // 30.2 -> 34.7, 56 pairs of 124 rows 34.2 -> 37.2
+        const int64_t wgs4 = pairs * ((group_rows * S::D + kCombineThreads - 1) / kCombineThreads);
+        if (a.nwg > kCombineSlots * pairs && wgs4 <= 8 * (int64_t)device_cus())
+            combine(std::integral_constant<int, 4>{});
         else combine(std::integral_constant<int, 1>{});
     });
 }
