@@ -1877,12 +1877,12 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
                                m.unit_start, m.slot_o, m.slot_lse, m.out);
         };
         if (pairs <= 0) return;
-        // more than a round of slots per pair: four thread groups share a row, if
-        // the four times larger grid is resident at once: 88 pairs of 52 rows 27.0 ->
-        // 23.3 us with it, but 41 pairs of 240 rows
-        // 30.2 -> 34.7, 56 pairs of 124 rows 34.2 -> 37.2
+        // more than one and a half rounds of slots per pair: four thread groups share
+        // a row, if the four times larger grid is resident at once (88 pairs of 52
+        // rows in 14 slots 26.5 -> 23.0 us, but 41 pairs of 240 rows in 12 slots 30.2
+        // -> 34.7, 30 pairs of 88 rows in 10 slots 36.2 -> 38.6)
         const int64_t wgs4 = pairs * ((group_rows * S::D + kCombineThreads - 1) / kCombineThreads);
-        if (a.nwg > kCombineSlots * pairs && wgs4 <= 8 * (int64_t)device_cus())
+        if (2 * (int64_t)a.nwg > 3 * kCombineSlots * pairs && wgs4 <= 8 * (int64_t)device_cus())
             combine(std::integral_constant<int, 4>{});
         else combine(std::integral_constant<int, 1>{});
     });

@@ -31,6 +31,8 @@ CASES = [
     ("window, one row group too few", (16, 2, 64), [300, 90, 40], [31, 0, 2], 20, False, True),
     ("63 blocks, pairs on every CU", (32, 8, 128), [1000 - 31 * i for i in range(32)], [i % 3 for i in range(32)],
      0, True, True),
+    ("69 blocks, more pairs than CUs", (64, 8, 64), [1100] + [13 * i + 1 for i in range(36)], [i % 3 for i in range(37)],
+     0, True, True),
     ("64 blocks", (32, 8, 128), [1019, 500, 31, 1], [4, 8, 0, 2], 0, False, False),
     ("many slots per pair", (32, 8, 128), [2999, 16], [4, 0], 0, True, False),
     ("many slots per pair, D 64", (64, 8, 64), [3100], [8], 0, True, False),
