@@ -123,46 +123,46 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// 16 bytes per lane from global memory straight into LDS (gfx950
-// global_load_lds_dwordx4): lane l of the wavefront writes LDS bytes
-// [lds + 16 l, lds + 16 l + 16).  The load is issued from inline assembly so
-// that its completion is tracked by the pipeline's explicit waits alone; the
-// compiler does not see it and adds no waits of its own.  m0 (the LDS base of
-// the copy) is set inside the same statement and listed as clobbered; nothing
-// else in these kernels uses m0 (no LDS-direct, movrel or message
-// instructions), so no value of the compiler's lives in it across the copy.
-__device__ __forceinline__ void dma16(uint32_t lds_wave_base, const void* src) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_wave_base)), "v"(src)
-                 : "memory", "m0");
-}
-
-// RUN consecutive KiB from global memory into LDS: load r moves bytes
+// RUN consecutive KiB from global memory straight into LDS (gfx950
+// global_load_lds_dwordx4, 16 bytes per lane): load r moves bytes
 // [src + 1024 r + 16 l, + 16) to LDS byte lds + 1024 r + 16 l of lane l
 // (lane16 = 16 l).  src is wavefront-uniform; the immediate offset applies to
-// the global and to the LDS address.
+// the global and to the LDS address.  The loads are issued from inline assembly
+// so that their completion is tracked by the pipeline's explicit waits alone;
+// the compiler does not see them and adds no waits of its own.  m0 (the LDS base
+// of the copy) is set inside the same statement and listed as clobbered; nothing
+// else in these kernels uses m0 (no LDS-direct, movrel or message
+// instructions), so no value of the compiler's lives in it across the copy.
+// Two waits that the hardware leaves to software are part of the statement too:
+// one state between the write of m0 and the first load, and five between a
+// vector instruction that wrote the base's registers (a readfirstlane the
+// compiler may leave right before the statement) and a load that reads them.
+// The scalar copy of the base is the first, and makes the second unnecessary:
+// scalar reads do wait for such writes.
 template <int RUN>
 __device__ __forceinline__ void dma16_run(uint32_t lds_wave_base, const void* src, uint32_t lane16) {
     static_assert(RUN == 1 || RUN == 2 || RUN == 4, "13-bit immediate offsets");
     const uint64_t u = (uint64_t)(uintptr_t)src;
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
-    const void* const base = (const void*)(uintptr_t)(((uint64_t)hi << 32) | lo);
+    const uint64_t base = ((uint64_t)hi << 32) | lo;
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_wave_base);
+    uint64_t from;  // the copy of base
     if constexpr (RUN == 4)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:3072"
-                     : : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\t"
+                     "global_load_lds_dwordx4 %2, %0\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:3072"
+                     : "=&s"(from) : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
     else if constexpr (RUN == 2)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:1024"
-                     : : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\t"
+                     "global_load_lds_dwordx4 %2, %0\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:1024"
+                     : "=&s"(from) : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     : : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                     : "=&s"(from) : "s"(m0), "v"(lane16), "s"(base) : "memory", "m0");
 }
 
 // Wait until at most N vector-memory operations of this wavefront are in flight.

@@ -21,7 +21,7 @@
 
 #include "common.h"
 
-// m0 is set inside the global->LDS load sequence (see dma16); the compiler
+// m0 is set inside the global->LDS load sequence (see dma16_run); the compiler
 // reloads m0 before each of its own uses, so clobbering it there is safe.
 #pragma clang diagnostic ignored "-Winline-asm"
 

@@ -136,12 +136,16 @@ __device__ __forceinline__ const void* uniform_ptr(const void* p) {
 // wavefront-uniform base and a per-lane 32-bit byte offset, the
 // global_load_lds_dwordx4 saddr form) into LDS bytes [lds + 16 l, lds + 16 l +
 // 16) of lane l.  The test is made inside the statement, so a skipped load
-// leaves no branch in the compiler's view of the surrounding products.
+// leaves no branch in the compiler's view of the surrounding products.  The
+// s_nop makes the statement's two waits: one state between the write of m0 and
+// the load, and five, with the instructions before it, between a vector
+// instruction that wrote the base's registers right before the statement and
+// the load that reads them.
 template <int C>
 __device__ __forceinline__ void dma16_if_lt(int n, uint32_t lds_wave_base, const void* sbase,
                                             uint32_t voff) {
     asm volatile("s_cmp_le_i32 %3, %4\n\ts_cbranch_scc1 1f\n\t"
-                 "s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2\n1:"
+                 "s_mov_b32 m0, %0\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %1, %2\n1:"
                  :
                  : "s"(__builtin_amdgcn_readfirstlane(lds_wave_base)), "v"(voff),
                    "s"(uniform_ptr(sbase)), "s"(n), "n"(C)
