@@ -208,7 +208,8 @@ def _workspace_arg(workspace, idx, device):
 
 def _layer_args(Hq, D, dtype, esize, idx, dev, k_cache, v_cache, block_tables, seq_lens, q_start):
     """Addresses of a layer's cache and batch descriptor, and its AttnParams
-    (sliding_window, scale and kv_split_blocks 0)."""
+    (sliding_window, scale and kv_split_blocks 0).  A batch of no requests may
+    come without seq_lens and q_start; the call refuses their absence otherwise."""
     import torch
     i32 = torch.int32
     if k_cache.dim() != 5:
@@ -221,8 +222,8 @@ def _layer_args(Hq, D, dtype, esize, idx, dev, k_cache, v_cache, block_tables, s
         raise ValueError("block_tables must be [B, max_blocks], got %s" % (tuple(block_tables.shape),))
     B, max_blocks = block_tables.shape
     ptrs += [_arg(block_tables, "block_tables", None, i32, idx, dev),
-             _arg(seq_lens, "seq_lens", (B,), i32, idx, dev),
-             _arg(q_start, "q_start", (B + 1,), i32, idx, dev)]
+             None if seq_lens is None else _arg(seq_lens, "seq_lens", (B,), i32, idx, dev),
+             None if q_start is None else _arg(q_start, "q_start", (B + 1,), i32, idx, dev)]
     return ptrs, AttnParams(B, Hq, hkv, D, 16, max_blocks, nb, 0, 0.0, _dtype_code(k_cache), 0)
 
 
@@ -640,7 +641,6 @@ def verify_kv_append(k_new, v_new, k_cache, v_cache, block_tables, seq_lens, q_s
     paged-cache slots (position S_i - n_i + j for row j of request i), in place.
     check: validate the descriptor and the new tokens' block ids on the device
     first (check_batch with a one-key window: only those blocks)."""
-    import torch
     if k_new.dim() != 3:
         raise ValueError("k_new must be [T, Hkv, D], got %s" % (tuple(k_new.shape),))
     _expect(v_new, "v_new", tuple(k_new.shape), k_new.dtype, k_new.device)

@@ -394,6 +394,23 @@ def test_binding_checks_tensor_shapes_dtypes_and_devices():
                             base["q_start"])
 
 
+@pytest.mark.parametrize("requests", [0, 4])
+def test_binding_leaves_a_missing_descriptor_to_the_call(requests):
+    """seq_lens and q_start may be None: a batch of no requests needs neither,
+    and the call itself refuses their absence (EINVAL) otherwise."""
+    m = dict(device="meta")
+    bf, i32 = torch.bfloat16, torch.int32
+    rows = torch.empty(0, 8, 128, dtype=bf, **m)
+    layer = (torch.empty(100, 8, 16, 16, 8, dtype=bf, **m), torch.empty(100, 8, 128, 16, dtype=bf, **m),
+             torch.empty(requests, 30, dtype=i32, **m))
+    with pytest.raises(ValueError, match="q must be a device tensor"):
+        av.verify_attention(rows, *layer, None, None, max_q_len=9, max_seq_len=480)
+    with pytest.raises(ValueError, match="q must be a device tensor"):
+        av.verify_attention_append(rows, rows, rows, *layer, None, None, max_q_len=9, max_seq_len=480)
+    with pytest.raises(ValueError, match="k_new must be a device tensor"):
+        av.verify_kv_append(rows, rows, *layer, None, torch.empty(requests + 1, dtype=i32, **m))
+
+
 def _plan(p, total_q, max_q, max_s):
     info = (ctypes.c_int32 * av.PLAN_INFO)()
     assert av.library().verify_attention_plan(ctypes.byref(p), total_q, max_q, max_s, info) == 0
