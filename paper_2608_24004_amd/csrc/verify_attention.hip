@@ -757,8 +757,9 @@ __device__ __forceinline__ void wait_blocks(int n) {
 // two-tile kernels are held to three (168 registers): three workgroups per
 // compute unit hide a step's chain of LDS reads, products and exponentials
 // better than two with deeper rings (long-row class of the 43 GB batch 4.97
-// against 5.06 ms).  The fused append's then keeps a few values in scratch,
-// reloaded only on pair switches and patched blocks.
+// against 5.06 ms).  The fused append's then keeps some values in scratch (and so
+// does its five-tile kernel at 256 registers), reloaded on pair switches, patched
+// blocks and in the steps between them and the steady state, which holds none.
 template <int TPW, int NW>
 constexpr int persist_waves_per_eu() { return TPW == 1 ? 4 : (NW == 4 && TPW == 2 ? 3 : 2); }
 
@@ -887,9 +888,14 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
     // Online softmax state per tile, in the log2 domain: m_r is the maximum
     // the row's exponentials are taken against (identical in the four lanes
     // that hold the row), thr the raw score above which a lane needs a new
-    // maximum, neg_m = -m_r (0 while the row has seen no key).
-    float m_r[TPW], l_r[TPW], thr[TPW], neg_m[TPW];
-    float sink_l2[TPW];  // the row's head's sink logit in the log2 domain (-inf: none)
+    // maximum, neg_m = -m_r (0 while the row has seen no key).  With five tiles
+    // m_r is taken from the other two where it is needed (rarely): its five
+    // registers, and five of sink logits that are now read when a pair is done,
+    // are what kept that kernel from fitting 256 (1024 pairs of 64 blocks at head
+    // dim 64: walk 62.6 -> 59.2 us).
+    constexpr bool KEEP_M = TPW < 5;
+    float m_kept[TPW], l_r[TPW], thr[TPW], neg_m[TPW];
+    auto m_r = [&](int t) { return KEEP_M ? m_kept[t] : thr[t] == -INFINITY ? -INFINITY : -neg_m[t]; };
     // APPEND: the pair's new-token positions [st_nlo, st_nhi) (those the walk
     // reaches) and the position of its first row, S_i - n_i
     int st_nlo = 0, st_nhi = 0, st_p0 = 0;
@@ -919,11 +925,10 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
                 if (valid) v = ld16(qg + base + (cc * 4 + lg) * 8);
                 qop[t][cc] = as_bf16x8(v);
             }
-            m_r[t] = -INFINITY;
+            m_kept[t] = -INFINITY;
             l_r[t] = 0.f;
             thr[t] = -INFINITY;
             neg_m[t] = 0.f;
-            sink_l2[t] = a.sinks && valid ? a.sinks[cc.g * a.group + gh] * kLog2e : -INFINITY;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) o[t][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         }
@@ -948,9 +953,9 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
             const int rr = cc.r * ROWS + lr;
             if (rr >= rows) continue;
             if (whole) {
-                const float den = L + (a.sinks ? exp2f(sink_l2[t] - m_r[t]) : 0.f);
-                const float inv = den > 0.f ? 1.f / den : 0.f;
                 const int j = rr / a.group, gh = rr - j * a.group;
+                const float den = L + sink_term(a.sinks, cc.g * a.group + gh, m_r(t));
+                const float inv = den > 0.f ? 1.f / den : 0.f;
                 const int64_t hrow = (int64_t)(cc.rq.q0 + j) * a.hq + cc.g * a.group + gh;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
@@ -970,7 +975,7 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
                     *reinterpret_cast<uint2*>(tb + dt * (kWave * 4)) =
                         make_uint2(pack_bf16x2(o[t][dt][0] * inv, o[t][dt][1] * inv),
                                    pack_bf16x2(o[t][dt][2] * inv, o[t][dt][3] * inv));
-                if (lg == 0) slot_lse[srow] = L > 0.f ? m_r[t] + log2f(L) : -INFINITY;
+                if (lg == 0) slot_lse[srow] = L > 0.f ? m_r(t) + log2f(L) : -INFINITY;
             }
         }
     };
@@ -1029,8 +1034,10 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
         uint32_t pw[TPW][2 * NB];
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
+            float m = m_r(t);
             softmax_step<NB, DT>(sacc[t], masked, row_j[t], p_first, key0, a.window, a.scale_log2,
-                                 a.inv_scale_log2, m_r[t], l_r[t], thr[t], neg_m[t], o[t], pw[t]);
+                                 a.inv_scale_log2, m, l_r[t], thr[t], neg_m[t], o[t], pw[t]);
+            m_kept[t] = m;
             if constexpr (NB == 2) {  // ascending keys
                 const uint32_t w0 = pw[t][0], w1 = pw[t][1];
                 pw[t][0] = b_lane ? pw[t][2] : w0;
@@ -1257,7 +1264,10 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
 // few pairs are cut into many (SG = 4), four thread groups share a row: each
 // takes every fourth round, and their sums are merged through LDS (24 slots:
 // three rounds of latency -> one; one request of 95 blocks, whole call 16.3 ->
-// 13.1 us).
+// 13.1 us).  Eight wavefronts per SIMD hide a round's latency; the partials stay
+// packed until they are added, which is what lets a round fit the 64 registers
+// that leaves (unpacked at once they went to scratch; one request 13.1 -> 12.6 us,
+// 512 pairs of up to 120 blocks and 4 rows 20.5 -> 19.4).
 constexpr int kCombineThreads = 256;
 constexpr int kCombineSlots = 8;
 
@@ -1306,12 +1316,11 @@ void attn_combine_slots(
             const int64_t slot0 = (int64_t)P + wf;
             const int ns = wl - wf + 1;
             for (int s0 = sg * kCombineSlots; s0 < ns; s0 += SG * kCombineSlots) {
-                float lse[kCombineSlots];
-                f32x4_t o[kCombineSlots];
                 // every load is issued unconditionally (slots past the pair's last
                 // re-read the last one and are masked afterwards), so that the
                 // round's loads leave back to back; conditional loads compiled to a
                 // branch and a wait per slot, one memory latency each
+                float lse[kCombineSlots];
                 uint2 v[kCombineSlots];
 #pragma unroll
                 for (int k = 0; k < kCombineSlots; ++k) {
@@ -1323,22 +1332,23 @@ void attn_combine_slots(
                 for (int k = 0; k < kCombineSlots; ++k) {
                     const bool in = s0 + k < ns;
                     lse[k] = in ? lse[k] : -INFINITY;
-                    o[k] = in ? f32x4_t{bf16_lo(v[k].x), bf16_hi(v[k].x), bf16_lo(v[k].y), bf16_hi(v[k].y)}
-                              : f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    v[k] = in ? v[k] : make_uint2(0u, 0u);
                 }
                 float m = M;
 #pragma unroll
                 for (int k = 0; k < kCombineSlots; ++k) m = fmaxf(m, lse[k]);
-                if (m == -INFINITY) continue;
+                // without a branch for m = -inf, below which the compiler would
+                // move the loads of the values, a second memory latency per round
+                const float mu = m == -INFINITY ? 0.f : m;
                 // rescale what earlier rounds summed (nothing yet: M = -inf gives 0)
-                const float r = __builtin_amdgcn_exp2f(M - m);
+                const float r = __builtin_amdgcn_exp2f(M - mu);
                 L *= r;
                 acc *= r;
 #pragma unroll
                 for (int k = 0; k < kCombineSlots; ++k) {
-                    const float f = lse[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(lse[k] - m);
+                    const float f = __builtin_amdgcn_exp2f(lse[k] - mu);
                     L += f;
-                    acc += f * o[k];
+                    acc += f * f32x4_t{bf16_lo(v[k].x), bf16_hi(v[k].x), bf16_lo(v[k].y), bf16_hi(v[k].y)};
                 }
                 M = m;
             }

@@ -1,15 +1,20 @@
-"""Wait states of the loads to LDS that are issued from inline assembly.
+"""What the compiled kernels must hold, read from their device assembly.
 
-The compiler does not look into such a statement, so the waits that the
-hardware leaves to software have to be part of it: one state between a scalar
-write of m0 and a load to LDS, and five between a vector instruction's write of
-a scalar register and a load that takes its address from it.  The device
-assembly of the two kernels that issue them is compiled here and read."""
+Wait states of the loads to LDS that are issued from inline assembly: the
+compiler does not look into such a statement, so the waits that the hardware
+leaves to software have to be part of it, one state between a scalar write of
+m0 and a load to LDS, and five between a vector instruction's write of a scalar
+register and a load that takes its address from it.
+
+Registers: the attention's walk and merge kernels keep what they work on in
+registers (the fused append's walks excepted, see persist_waves_per_eu)."""
 from __future__ import annotations
 
+import functools
 import os
 import re
 import subprocess
+import tempfile
 
 import pytest
 
@@ -75,18 +80,34 @@ def _faults(asm):
     return loads, bad
 
 
+@functools.lru_cache(maxsize=None)
+def _assembly(name):
+    with tempfile.TemporaryDirectory() as tmp:
+        src = os.path.join(CSRC, name)
+        if name == "probe.hip":
+            src = os.path.join(tmp, name)
+            with open(src, "w") as f:
+                f.write(PROBE)
+        out = os.path.join(tmp, "device.s")
+        flags = [f for f in build.HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-Wall")]
+        subprocess.run([build.hipcc()] + flags + ["--cuda-device-only", "-S", "-I", os.path.join(build.ROOT, "include"),
+                                                  "-I", CSRC, "-o", out, src], check=True, stderr=subprocess.DEVNULL)
+        with open(out) as f:
+            return f.read()
+
+
 @pytest.mark.parametrize("name", ["verify_attention.hip", "verify_lmhead.hip", "probe.hip"])
-def test_loads_to_lds_wait_for_their_scalars(tmp_path, name):
-    src = os.path.join(CSRC, name)
-    if name == "probe.hip":
-        src = str(tmp_path / name)
-        with open(src, "w") as f:
-            f.write(PROBE)
-    out = str(tmp_path / "device.s")
-    flags = [f for f in build.HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-Wall")]
-    subprocess.run([build.hipcc()] + flags + ["--cuda-device-only", "-S", "-I", os.path.join(build.ROOT, "include"),
-                                              "-I", CSRC, "-o", out, src], check=True, stderr=subprocess.DEVNULL)
-    with open(out) as f:
-        loads, bad = _faults(f.read())
+def test_loads_to_lds_wait_for_their_scalars(name):
+    loads, bad = _faults(_assembly(name))
     assert loads >= 7
     assert not bad, "%d of %d loads, first: %s" % (len(bad), loads, bad[0])
+
+
+def test_attention_kernels_do_not_spill():
+    scratch = {}
+    for block in re.split(r"\n  - \.agpr_count", _assembly("verify_attention.hip"))[1:]:
+        name = re.search(r"\.name:\s+(\S+)", block)[1]
+        scratch[name] = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", block)[1])
+    plain = {n: b for n, b in scratch.items() if re.search(r"attn_(persist|combine|f32)", n) and "Lb1E" not in n}
+    assert len(plain) >= 20
+    assert not {n: b for n, b in plain.items() if b}
