@@ -17,6 +17,7 @@
 // t <= p, and with a sliding window W only t > p - W; the walk covers the
 // union of the rows' visible blocks only.
 #include <atomic>
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -1593,14 +1594,28 @@ constexpr int kShortClassRows = 48;
 // than the balance gains).
 constexpr int64_t kOversubUnits = 4096;
 
-// Slots a pair of the longest length is cut into at most (with the resident
-// workgroups it is often fewer); no workgroup takes fewer than two blocks.
-// More workgroups shorten the walk of a small batch, but each adds a slot per
-// pair that the merge reads.  One request of 95 blocks on eight KV heads, walk and merge together:
-// 24.6 us with a workgroup per block (95 slots a pair), 13.9 / 13.1 / 13.5 /
-// 14.4 us with at least 2 / 4 / 6 / 8 blocks per workgroup; 32 blocks: 9.5 us
-// with 2, 10.7 with 4; 251 blocks: 19.7, 17.3 and with 12 blocks 15.1 us.
-constexpr int kSlotsPerPair = 24;
+// Ranges that a plan of few pairs cuts a pair of the longest length into.  More
+// workgroups shorten the walk (0.28 us per block and workgroup on an idle chip),
+// but each adds a slot per pair that the merge reads, 32 of them in a round of
+// about 1.1 us where four thread groups share a row.  The sum is least at
+// sqrt(8.2 blocks) ranges: 28 of 95 blocks, 91 of 1001, 259 of 8188.  Measured
+// on one request (us for 24 / 32 / 48 / 64 / 96 / 128 / 192 / 256 ranges; eight
+// KV heads: 251 blocks 16.8 / 16.6 / 17.3 / 16.7 / 17.8; 1001 blocks 29.1 / 27.3 /
+// 26.4 / 26.8 / 25.4 / 27.3 / 31.8 / 36.3; one KV head, 8188 blocks 210 / 161 /
+// 114 / 90 / 67 / 57 / 47 / 43).  Beyond about two thirds of the resident
+// workgroups in the launch more of them only lengthen the merge (32 pairs of 1001
+// blocks: 52 us with 768, 54 with 1024, 60 with 2048).  Multiples of 30, so that
+// a pair with a range boundary off its ends still has whole rounds of slots; at
+// least kMinRanges (95 blocks: 13.7 us with 24 ranges, 14.4 with 16), and no range
+// planned below two blocks.  These are the plan's figures, for pairs as long as
+// the longest may be: where lengths differ, a long pair gets more than its share
+// of the ranges, and where they all are shorter, ranges of one block occur.
+constexpr int kMinRanges = 24;
+
+int64_t ranges_per_pair(int64_t nb_max, int64_t pairs, int64_t resident) {
+    const int64_t best = std::min((int64_t)std::sqrt(8.2 * (double)nb_max), 2 * resident / (3 * pairs));
+    return best < 30 ? kMinRanges : best / 30 * 30;
+}
 
 // Whether a launch gives every pair to one workgroup: no schedule scan, no
 // partial slots and no merge launch, at the price of a walk as long as the
@@ -1764,8 +1779,9 @@ int plan_class(const verify_attn_params* p, int64_t rows, int64_t nb_max, int ro
                 res = append ? resident_wgs<decltype(sh), true>() : resident_wgs<decltype(sh)>();
             }))
             return VERIFY_EUNSUPPORTED;
-        const int64_t apart = std::max<int64_t>(2, (nb_max + kSlotsPerPair - 1) / kSlotsPerPair);
-        const int64_t resident = std::min<int64_t>((int64_t)device_cus() * res, (units_max + apart - 1) / apart);
+        const int64_t all = (int64_t)device_cus() * res, ranges = ranges_per_pair(nb_max, pairs, all);
+        const int64_t apart = std::max<int64_t>(2, (nb_max + ranges - 1) / ranges);
+        const int64_t resident = std::min(all, (units_max + apart - 1) / apart);
         const int64_t mult = std::min<int64_t>(8, std::max<int64_t>(1, units_max / resident / kOversubUnits));
         c.nwg = (int)(resident * mult);
     }

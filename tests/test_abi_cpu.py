@@ -455,3 +455,14 @@ def test_attention_plan_row_classes():
     plan = av.attention_plan(qt, kc, bt, max_q_len=33, max_seq_len=16393)
     assert [c["rows_lo"] for c in plan["classes"]] == [0, 49]
     assert plan["classes"][0]["rows_hi"] == 48 and plan["rows_per_group"] == 48
+
+
+@pytest.mark.parametrize("hkv, blocks, least", [(1, 8193, 180), (2, 8193, 140), (4, 4096, 50), (1, 501, 50)])
+def test_attention_plan_spreads_few_long_pairs(hkv, blocks, least):
+    """One request of a long context: the plan cuts its pairs into more ranges as
+    they grow (24 ranges each before), up to about two thirds
+    of the resident workgroups (512 without a GPU), and a short one as before."""
+    info = _plan(_params(num_seqs=1, num_q_heads=4 * hkv, num_kv_heads=hkv, max_blocks_per_seq=blocks), 5, 5,
+                 16 * blocks)
+    assert info[4] == 0 and least * hkv <= info[1] <= 512
+    assert _plan(_params(num_seqs=1), 5, 5, 1505)[1] == 8 * 95 // 4  # 95 blocks, eight KV heads: 24 ranges each
