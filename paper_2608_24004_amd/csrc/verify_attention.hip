@@ -1619,20 +1619,26 @@ int64_t ranges_per_pair(int64_t nb_max, int64_t pairs, int64_t resident) {
 
 // Whether a launch gives every pair to one workgroup: no schedule scan, no
 // partial slots and no merge launch, at the price of a walk as long as the
-// longest pair.  The walk of one workgroup takes 0.28 us per block on an idle
-// chip, the schedule, the slots and the merge about 6 us, so up to 16 blocks
-// whole pairs are always faster (8 KV heads of one request, 16 blocks: 10.2
-// against 10.7 us, 32 blocks 14.7 against 9.5 us).  Where the pairs fill the
-// compute units the walk is not longer than a share of the batch's: 256 pairs
-// of 32 / 63 blocks 16.5 / 31.4 against 23.3 / 37.6 us, 1024 pairs of 63
-// blocks 99 against 106 us (head dim 128) and 63 against 89 us (head dim 64).
-// From half a pair per compute unit on the line rises with the pairs (30 pairs
-// of 21 blocks and up to eight tiles lost 36.2 -> 38.6 us whole), to 127 blocks;
-// the several-tile one-wavefront shapes, which start at 64 blocks, stay below
-// that: a pair would be one wavefront's alone.
-bool whole_pairs(int64_t nb_max, int64_t pairs, int64_t cus, bool one_wave_many_tiles) {
-    if (nb_max > (one_wave_many_tiles ? 63 : 127)) return false;
-    return nb_max <= 16 + (2 * pairs >= cus ? 48 * pairs / cus : 0);
+// longest pair.  Up to 16 blocks whole pairs are always faster (8 KV heads of one
+// request, 16 blocks: 10.2 against 10.7 us, 32 blocks 14.7 against 9.5 us).
+// Beyond that they are where the pairs fill the compute units and their lengths
+// are alike: 256 pairs of 32 blocks 20.2 against 28.8 us, 512 of 88 blocks 64
+// against 86.  But the plan does not see the lengths, and the longest pair may be
+// long alone; the lines lie where that costs what the cut walk does.  One request
+// at the longest length among requests of two or three blocks, whole against cut:
+//   one wavefront: 17 blocks 12 against 13 us, 26 to 33 16.6 against 15.7, 40
+//     18 against 14, 64 25 against 17;
+//   several of one tile: 64 blocks 24 against 33 us, 88 blocks 25 to 31 against
+//     35 to 43;
+//   several of more tiles: 64 blocks 42 against 62 us, 88 blocks 45 to 55 against
+//     41 to 48.
+// With fewer pairs the line comes down to the 16 blocks (30 pairs of 21 blocks and
+// up to eight tiles 38.6 whole against 36.2 us).  pairs counts those that can
+// have rows: a launch of long rows is not filled by the requests of the other one.
+bool whole_pairs(int64_t nb_max, int64_t pairs, int64_t cus, int nw, int tpw) {
+    if (nb_max <= 16) return true;
+    const int64_t most = nw == 1 ? 28 : tpw == 1 ? 95 : 72;
+    return 2 * pairs >= cus && nb_max <= std::min(most, 16 + 48 * pairs / cus);
 }
 
 // LDS stages (blocks) of a workgroup's ring.  A step computes two of them while
@@ -1757,8 +1763,8 @@ void pick_shape(int head_dim, int64_t tiles, int64_t nb_max, int& nw, int& tpw) 
 
 // The persistent launch of one row class: requests with rows_lo <= Hq/Hkv *
 // n_i <= rows_hi, of which no request has more than `rows` rows.
-int plan_class(const verify_attn_params* p, int64_t rows, int64_t nb_max, int rows_lo, int rows_hi,
-               bool append, AttnPlan::Class& c) {
+int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64_t nb_max, int rows_lo,
+               int rows_hi, bool append, AttnPlan::Class& c) {
     c = AttnPlan::Class{};
     pick_shape(p->head_dim, (rows + 15) / 16, nb_max, c.nw, c.tpw);
     c.rows_lo = rows_lo;
@@ -1766,6 +1772,10 @@ int plan_class(const verify_attn_params* p, int64_t rows, int64_t nb_max, int ro
     const int64_t per = (int64_t)c.nw * c.tpw * 16;
     c.rg_max = (int)((rows + per - 1) / per);
     const int64_t pairs = (int64_t)std::max(1, p->num_seqs) * p->num_kv_heads * c.rg_max;
+    // of which so many at most have rows in the class
+    const int64_t active = rows_lo > 0 ? (int64_t)total_q * (p->num_q_heads / p->num_kv_heads) / rows_lo *
+                                             p->num_kv_heads * c.rg_max
+                                       : pairs;
     const int64_t units_max = pairs * nb_max;
     if (units_max >= (int64_t)1 << 31) return VERIFY_EUNSUPPORTED;
     c.spb = p->kv_split_blocks;
@@ -1786,7 +1796,7 @@ int plan_class(const verify_attn_params* p, int64_t rows, int64_t nb_max, int ro
         c.nwg = (int)(resident * mult);
     }
     c.slots = pairs + c.nwg;
-    if (c.spb == 0 && whole_pairs(nb_max, pairs, device_cus(), c.nw == 1 && c.tpw > 1)) {
+    if (c.spb == 0 && whole_pairs(nb_max, std::min(pairs, active), device_cus(), c.nw, c.tpw)) {
         c.whole = true;
         c.nwg = (int)pairs;
         c.slots = 0;
@@ -1831,12 +1841,12 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
         int rc;
         if (p->head_dim == 128 && (rows + 15) / 16 >= 5) {
             pl.nclass = 2;
-            rc = plan_class(p, kShortClassRows, nb_max, 0, kShortClassRows, append, pl.cls[0]);
+            rc = plan_class(p, total_q, kShortClassRows, nb_max, 0, kShortClassRows, append, pl.cls[0]);
             if (rc == VERIFY_OK)
-                rc = plan_class(p, rows, nb_max, kShortClassRows + 1, INT32_MAX, append, pl.cls[1]);
+                rc = plan_class(p, total_q, rows, nb_max, kShortClassRows + 1, INT32_MAX, append, pl.cls[1]);
         } else {
             pl.nclass = 1;
-            rc = plan_class(p, rows, nb_max, 0, INT32_MAX, append, pl.cls[0]);
+            rc = plan_class(p, total_q, rows, nb_max, 0, INT32_MAX, append, pl.cls[0]);
         }
         if (rc != VERIFY_OK) return rc;
         size_t off = 0;

@@ -466,3 +466,24 @@ def test_attention_plan_spreads_few_long_pairs(hkv, blocks, least):
                  16 * blocks)
     assert info[4] == 0 and least * hkv <= info[1] <= 512
     assert _plan(_params(num_seqs=1), 5, 5, 1505)[1] == 8 * 95 // 4  # 95 blocks, eight KV heads: 24 ranges each
+
+
+def test_attention_plan_whole_pairs_are_safe_for_uneven_lengths():
+    """The plan gives pairs whole to a workgroup only where one long request
+    among short ones costs no more than cutting it: up to 28 blocks on one
+    wavefront, 95 on several of one tile, 72 of more; and it does not take the
+    requests of the other row class for pairs that fill the chip."""
+    def units(blocks, drafts, requests=32, total_q=None, **kw):
+        rows = drafts + 1
+        info = _plan(_params(num_seqs=requests, max_blocks_per_seq=blocks, **kw), total_q or requests * rows, rows,
+                     16 * blocks)
+        return [info[4], info[9]][:info[5]]
+
+    assert units(28, 0) == [-1] and units(29, 0) == [0]        # one tile, one wavefront
+    assert units(63, 4) == [-1] and units(96, 4, 64) == [0]    # two tiles on two wavefronts
+    assert units(95, 4, 64) == [-1]
+    assert units(63, 13) == [-1] and units(72, 13, 64) == [-1] and units(73, 13, 64) == [0]  # two tiles each
+    assert units(16, 0, 1) == [-1] and units(17, 0, 1) == [0]  # few pairs
+    # two row classes of 64 requests: all can be long, or (62 rows of four, two of 17) 23 of them
+    assert units(63, 16, 64) == [-1, -1]
+    assert units(63, 16, 64, total_q=62 * 4 + 2 * 17) == [-1, 0]

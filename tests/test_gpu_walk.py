@@ -29,7 +29,12 @@ CASES = [
     ("17 blocks, few pairs", (8, 2, 128), [260, 31], [4, 0], 0, False, False),
     ("window of 9 to 10 blocks", (64, 8, 64), [4000, 130, 17, 900, 143], [5, 0, 16, 9, 8], 128, True, True),
     ("window, one row group too few", (16, 2, 64), [300, 90, 40], [31, 0, 2], 20, False, True),
+    # twelve rows at most: one tile, whose pairs are cut beyond 28 blocks
     ("63 blocks, pairs on every CU", (32, 8, 128), [1000 - 31 * i for i in range(32)], [i % 3 for i in range(32)],
+     0, True, False),
+    ("63 blocks, two tiles, pairs on every CU", (32, 8, 128), [1000 - 31 * i for i in range(32)],
+     [i % 6 for i in range(32)], 0, True, True),
+    ("28 blocks, one tile, one long", (32, 8, 128), [445] + [3 * i for i in range(31)], [i % 3 for i in range(32)],
      0, True, True),
     ("69 blocks, more pairs than CUs", (64, 8, 64), [1100] + [13 * i + 1 for i in range(36)], [i % 3 for i in range(37)],
      0, True, True),
