@@ -18,6 +18,8 @@
 #include <atomic>
 #include <mutex>
 
+#include <type_traits>
+
 #include "common.h"
 
 // Scratch of verify_accept_noalloc (the per-(row, chunk) maxima, then the
@@ -181,8 +183,9 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_chunks(
 // below a score already reached in the chunk can be neither the row's maximum
 // nor tied with it.  The others are queued per wavefront in LDS and evaluated
 // 64 at a time, one per lane, so the logs run on full wavefronts.  The
-// threshold starts at the best score of the workgroup's most promising first
-// logits and is raised to the wavefront's best after every batch.  Arithmetic
+// threshold is the wavefront's best evaluated score, raised after every batch;
+// in long chunks it starts at the best score of the workgroup's most promising
+// first logits.  Arithmetic
 // bounds it (384 rows of 128256 bf16 logits: 2.5e7 vector instructions, the
 // 64-bit products among them no slower than the rest), so instructions are what
 // it saves: one three-way xor per generator word, one test for the four logits of
@@ -260,6 +263,16 @@ constexpr float kGumbelMax = 16.64f;  // >= gumbel_bound(k) for every k (n = 1: 
 
 constexpr int kSampleQueue = 2 * kWave;  // entries per wavefront queue
 constexpr int kSampleUnroll = 2;         // 16-byte vectors per lane per iteration
+
+// Chunks of more logits per thread than this find a first threshold before
+// they are scanned, at the price of evaluating one more vector per thread, a
+// barrier, and the scan that goes with a threshold (all of a vector's generator
+// words at once, tested by fours; without one the threshold rises from one four
+// to the next).  Above it, us with a first threshold / without: 24 bf16 logits per
+// thread 26.5 / 27.9 and 29.4 / 31.9, 42 vectors of fp32 124 / 140 (the scan of
+// before); below: 16 fp32 logits 25.3 / 25.6, 16 bf16 24.5 / 23.7 and 18.8 / 18.1,
+// 12 fp32 21.0 / 20.4, one vector 18.3 / 16.6 (fp32) and 20.5 / 17.9 (bf16).
+constexpr int kPrimeLogits = 16;
 
 template <typename T>
 __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
@@ -339,11 +352,12 @@ __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
     };
     // One 16-byte vector of E logits at element `base`; `have` is false for
     // lanes past the chunk's last vector, which still take part in the ballots.
-    auto scan = [&](const uint4& v, uint32_t base, bool have) {
+    auto scan = [&](auto primed, const uint4& v, uint32_t base, bool have) {
+        constexpr bool PRIMED = decltype(primed)::value;
         float x[E];
         unpack16(v, x, T());
         const bool nan = have && ((E == 8) ? any_nan_bf16x8(v) : any_nan_f32x4(v));
-        if (__ballot(nan) != 0 && nan && nan_idx == kNone) {
+        if (nan && nan_idx == kNone) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 if (x[e] != x[e]) { nan_idx = base + e; break; }
@@ -352,33 +366,39 @@ __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
         // a lane that holds a NaN reports it; its other logits drop out
         const bool live = have && nan_idx == kNone;
         float xm[E / 4];
-        bool any = false;
+        bool any[E / 4], some = false;
 #pragma unroll
         for (int b = 0; b < E / 4; ++b) {
             xm[b] = fmaxf(fmaxf(x[4 * b], x[4 * b + 1]), fmaxf(x[4 * b + 2], x[4 * b + 3]));
-            any |= fmaf(xm[b], sp.inv_t, kGumbelMax) >= thr;
+            any[b] = live && fmaf(xm[b], sp.inv_t, kGumbelMax) >= thr;
+            some |= any[b];
         }
-        if (__ballot(live && any) == 0) return;
         uint32_t w[E / 4][4];
-        bool may[E / 4], some = false;
+        if constexpr (PRIMED) {
+            if (__ballot(some) == 0) return;
+            some = false;
 #pragma unroll
-        for (int b = 0; b < E / 4; ++b) {
-            philox4x32_10((base >> 2) + b, urow, sp.offset, 0u, sp.k0, sp.k1, w[b]);
-            // the bound rises with the code and the score with both, so the
-            // largest logit under the largest code's bound covers the block's four
-            const uint32_t wmax = max(max(w[b][0], w[b][1]), max(w[b][2], w[b][3]));
-            may[b] = live && fmaf(xm[b], sp.inv_t, gumbel_bound(wmax >> 9)) >= thr;
-            some |= may[b];
+            for (int b = 0; b < E / 4; ++b) {
+                philox4x32_10((base >> 2) + b, urow, sp.offset, 0u, sp.k0, sp.k1, w[b]);
+                // the bound rises with the code and the score with both, so the
+                // largest logit under the largest code's bound covers the block's four
+                const uint32_t wmax = max(max(w[b][0], w[b][1]), max(w[b][2], w[b][3]));
+                any[b] = live && fmaf(xm[b], sp.inv_t, gumbel_bound(wmax >> 9)) >= thr;
+                some |= any[b];
+            }
+            if (__ballot(some) == 0) return;
         }
-        if (__ballot(some) == 0) return;
 #pragma unroll
         for (int b = 0; b < E / 4; ++b) {
-            if (__ballot(may[b]) == 0) continue;
+            // without a first threshold it rises from block to block
+            if constexpr (!PRIMED) any[b] = live && fmaf(xm[b], sp.inv_t, kGumbelMax) >= thr;
+            if (__ballot(any[b]) == 0) continue;
+            if constexpr (!PRIMED) philox4x32_10((base >> 2) + b, urow, sp.offset, 0u, sp.k0, sp.k1, w[b]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t k = w[b][e] >> 9;
                 const float xe = x[4 * b + e];
-                const bool cand = may[b] && fmaf(xe, sp.inv_t, gumbel_bound(k)) >= thr;
+                const bool cand = any[b] && fmaf(xe, sp.inv_t, gumbel_bound(k)) >= thr;
                 const uint64_t bal = __ballot(cand);
                 if (bal == 0) continue;
                 if (cand) {
@@ -418,24 +438,29 @@ __global__ __launch_bounds__(kArgmaxThreads) void sample_chunks(
                 dst[u] = vi < nvec ? ld16_stream(vp + vi) : make_uint4(0u, 0u, 0u, 0u);
             }
         };
-        if (wave_first < nvec) {
-            load(0, cur);
-            prime(cur[0], (uint32_t)(lo + (int64_t)tid * E), tid < nvec);
-        }
-        if (lane == 0) first[wid] = thr;
-        __syncthreads();
+        if (wave_first < nvec) load(0, cur);
+        auto walk = [&](auto primed) {
+            for (int64_t v0 = 0; v0 + wave_first < nvec; v0 += kStep) {
+                if (v0 + kStep + wave_first < nvec) load(v0 + kStep, nxt);
 #pragma unroll
-        for (int w = 0; w < kArgmaxThreads / kWave; ++w) thr = fmaxf(thr, first[w]);
-        thr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(thr)));
-        for (int64_t v0 = 0; v0 + wave_first < nvec; v0 += kStep) {
-            if (v0 + kStep + wave_first < nvec) load(v0 + kStep, nxt);
+                for (int u = 0; u < kSampleUnroll; ++u) {
+                    const int64_t vi = v0 + u * kArgmaxThreads + tid;
+                    scan(primed, cur[u], (uint32_t)(lo + vi * E), vi < nvec);
+                }
 #pragma unroll
-            for (int u = 0; u < kSampleUnroll; ++u) {
-                const int64_t vi = v0 + u * kArgmaxThreads + tid;
-                scan(cur[u], (uint32_t)(lo + vi * E), vi < nvec);
+                for (int u = 0; u < kSampleUnroll; ++u) cur[u] = nxt[u];
             }
+        };
+        if (hi - lo > (int64_t)kPrimeLogits * kArgmaxThreads) {
+            if (wave_first < nvec) prime(cur[0], (uint32_t)(lo + (int64_t)tid * E), tid < nvec);
+            if (lane == 0) first[wid] = thr;
+            __syncthreads();
 #pragma unroll
-            for (int u = 0; u < kSampleUnroll; ++u) cur[u] = nxt[u];
+            for (int w = 0; w < kArgmaxThreads / kWave; ++w) thr = fmaxf(thr, first[w]);
+            thr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(thr)));
+            walk(std::true_type{});
+        } else {
+            walk(std::false_type{});
         }
         for (int64_t e = lo + nvec * E + tid; e < hi; e += kArgmaxThreads) one(e);
     } else {

@@ -127,6 +127,26 @@ def test_sampled_edge_cases(dtype, vocab, fill, T):
     _check(got, want)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("more", [0, 64, 64 * 8 + 5], ids=["at", "one vector above", "last chunk below"])
+def test_sampled_chunks_at_the_first_threshold(dtype, more):
+    """64 rows are cut into chunks of a 64th of the vocabulary, rounded up: 16
+    logits per thread (scanned without a first threshold), and just above (with
+    one, the last, shorter chunk without); with and without special values."""
+    vocab = 64 * 4096 + more
+    say("sampled chunks", dtype, vocab)
+    rng = np.random.default_rng(vocab)
+    x = _specials(rng, (64, vocab))
+    x[32:] = rng.standard_normal((32, vocab)) * np.linspace(0.1, 8, 32)[:, None]
+    logits = torch.as_tensor(x, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32).to(DEV)
+    q_start = np.arange(0, 65, 8, dtype=np.int32)
+    code = workload.dtype_code(dtype)
+    y = oracle.sample(workload.host_storage(logits), code, 0.7, seed=5, offset=2)
+    tokens = _plant(y, q_start, rng, vocab)
+    want = _oracle_all(logits, q_start, tokens, code, 0.7, 5, 2)
+    _check(_gpu(logits, torch.as_tensor(tokens, device=DEV), torch.as_tensor(q_start, device=DEV), 0.7, 5, 2), want)
+
+
 def test_sampled_seeds_offsets_and_extreme_temperatures():
     rng = np.random.default_rng(5)
     V, R = 5000, 96
