@@ -458,8 +458,8 @@ struct MPtrs {
     const int32_t* q_start;
     uint16_t* out;
     int32_t* unit_start;  // [num_seqs + 1] first unit of each request (schedule pass)
-    uint16_t* slot_o;     // [slots][rows_per_group][D] normalised partial outputs, bf16
-                          // (slot_o_index)
+    void* slot_o;         // [slots][rows_per_group][D] normalised partial outputs, fp32 or
+                          // bf16 (slot_o_index)
     float* slot_lse;      // [slots][rows_per_group]    their log2-sum-exp
     const uint16_t* k_new;  // fused append: [total_q][Hkv][D] new keys, or null
     const uint16_t* v_new;  //               and values
@@ -472,11 +472,18 @@ struct ReqGeom {
 // Offset in slot_o of row lr (within the row group), dims d .. d+3 (d % 4 ==
 // 0), of slot `slot`.  Each 16-row tile of a slot is stored in the order the
 // MFMA output registers hold it: 16-dim column block dt, then lane
-// 16 (d / 4 % 4) + lr % 16, then the four dims.  The partial outputs are
-// stored in bf16 (the log2-sum-exp in fp32), as a split-K merge usually keeps
-// them in the output's type: they are normalised, so rounding them adds at most
-// 2^-9 relative error to the merged row, and it halves the bytes written at
-// the end of every range and read back by the merge.
+// 16 (d / 4 % 4) + lr % 16, then the four dims.
+//
+// A launch that fills the chip stores the partial outputs in bf16 (the
+// log2-sum-exp in fp32), as a split-K merge usually keeps them in the output's
+// type: they are normalised, so rounding them adds at most 2^-9 relative error to
+// the merged row, and it halves the bytes written at the end of every range and
+// read back by the merge.  A launch of few pairs cuts them into fewer ranges than
+// would fill the chip, so there are fewer roundings to average out and fewer
+// weights that are exactly 1 (one request of 95 blocks, error against 64 bits
+// 2.55e-3 with a range per block, 2.75e-3 with 24): its partials stay in fp32
+// (2.19e-3; the call 12.7 -> 12.8 us, at most 2 us where 30 pairs have eight
+// tiles: 23.7 -> 25.5).
 template <int D>
 __device__ __forceinline__ int64_t slot_o_index(int64_t slot, int rows_per_group, int lr, int d) {
     const int lane = ((d >> 2) & 3) * 16 + (lr & 15);
@@ -771,14 +778,16 @@ constexpr int persist_waves_per_eu() { return TPW == 1 ? 4 : (NW == 4 && TPW == 
 // those blocks only), and the workgroup of the pair's first row group also
 // stores them into the cache.  Readers never depend on that store, so no
 // ordering between workgroups is needed.
-template <int D, int NW, int TPW, int NS, bool APPEND>
+//
+// Slot: the type of the partial outputs (uint16_t: bf16, or float; slot_o_index).
+template <int D, int NW, int TPW, int NS, bool APPEND, typename Slot>
 __global__ __launch_bounds__(NW * kWave)
 __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_persist(
     PArgs a, const uint16_t* __restrict__ qg, const uint8_t* __restrict__ kcg,
     const uint8_t* __restrict__ vcg, const int32_t* __restrict__ block_tables,
     const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_start,
     int32_t* __restrict__ unit_start, uint16_t* __restrict__ out,
-    uint16_t* __restrict__ slot_o, float* __restrict__ slot_lse,
+    Slot* __restrict__ slot_o, float* __restrict__ slot_lse,
     const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new) {
     constexpr int NT = NW * kWave;
     constexpr int TILE_BYTES = kBlockTokens * D * 2;  // one (block, head) K or V tile
@@ -967,15 +976,19 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
                 }
             } else {
                 // the tile's 16 rows x D values in register order (see
-                // slot_o_index): each store writes 512 bytes contiguous
+                // slot_o_index): each store writes 512 bytes (fp32: 1 KiB) contiguous
                 const float inv = L > 0.f ? 1.f / L : 0.f;
                 const int64_t srow = slot * ROWS + lr;
-                uint16_t* tb = slot_o + (slot * ROWS + (wv * TPW + t) * 16) * D + lane * 4;
+                Slot* tb = slot_o + (slot * ROWS + (wv * TPW + t) * 16) * D + lane * 4;
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
-                    *reinterpret_cast<uint2*>(tb + dt * (kWave * 4)) =
-                        make_uint2(pack_bf16x2(o[t][dt][0] * inv, o[t][dt][1] * inv),
-                                   pack_bf16x2(o[t][dt][2] * inv, o[t][dt][3] * inv));
+                for (int dt = 0; dt < DT; ++dt) {
+                    if constexpr (sizeof(Slot) == 4)
+                        *reinterpret_cast<f32x4_t*>(tb + dt * (kWave * 4)) = o[t][dt] * inv;
+                    else
+                        *reinterpret_cast<uint2*>(tb + dt * (kWave * 4)) =
+                            make_uint2(pack_bf16x2(o[t][dt][0] * inv, o[t][dt][1] * inv),
+                                       pack_bf16x2(o[t][dt][2] * inv, o[t][dt][3] * inv));
+                }
                 if (lg == 0) slot_lse[srow] = L > 0.f ? m_r(t) + log2f(L) : -INFINITY;
             }
         }
@@ -1272,11 +1285,18 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
 constexpr int kCombineThreads = 256;
 constexpr int kCombineSlots = 8;
 
-template <int D, int SG>
-__global__ __launch_bounds__(kCombineThreads) __attribute__((amdgpu_waves_per_eu(8)))
+// The four partial values of a slot, as they are stored: bf16 pairs, or fp32.
+__device__ __forceinline__ f32x4_t unpack4(const uint2& v) {
+    return f32x4_t{bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y)};
+}
+__device__ __forceinline__ f32x4_t unpack4(const f32x4_t& v) { return v; }
+
+// Four: what holds four partial values (uint2 or f32x4_t).
+template <int D, int SG, typename Four>
+__global__ __launch_bounds__(kCombineThreads) __attribute__((amdgpu_waves_per_eu(sizeof(Four) == 8 ? 8 : 5)))
 void attn_combine_slots(
     PArgs a, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_start,
-    const int32_t* __restrict__ unit_start, const uint16_t* __restrict__ slot_o,
+    const int32_t* __restrict__ unit_start, const void* __restrict__ slot_o,
     const float* __restrict__ slot_lse, uint16_t* __restrict__ out) {
     constexpr int QUADS = D / 4;                       // 4-dim vectors per row
     constexpr int RPB = kCombineThreads / QUADS / SG;  // rows per workgroup
@@ -1322,18 +1342,18 @@ void attn_combine_slots(
                 // round's loads leave back to back; conditional loads compiled to a
                 // branch and a wait per slot, one memory latency each
                 float lse[kCombineSlots];
-                uint2 v[kCombineSlots];
+                Four v[kCombineSlots];
 #pragma unroll
                 for (int k = 0; k < kCombineSlots; ++k) {
                     const int64_t sl = slot0 + min(s0 + k, ns - 1);
                     lse[k] = slot_lse[sl * ROWS + lr];
-                    v[k] = *reinterpret_cast<const uint2*>(slot_o + slot_o_index<D>(sl, ROWS, lr, d0));
+                    v[k] = static_cast<const Four*>(slot_o)[slot_o_index<D>(sl, ROWS, lr, d0) / 4];
                 }
 #pragma unroll
                 for (int k = 0; k < kCombineSlots; ++k) {
                     const bool in = s0 + k < ns;
                     lse[k] = in ? lse[k] : -INFINITY;
-                    v[k] = in ? v[k] : make_uint2(0u, 0u);
+                    v[k] = in ? v[k] : Four{};
                 }
                 float m = M;
 #pragma unroll
@@ -1349,7 +1369,7 @@ void attn_combine_slots(
                 for (int k = 0; k < kCombineSlots; ++k) {
                     const float f = __builtin_amdgcn_exp2f(lse[k] - mu);
                     L += f;
-                    acc += f * f32x4_t{bf16_lo(v[k].x), bf16_hi(v[k].x), bf16_lo(v[k].y), bf16_hi(v[k].y)};
+                    acc += f * unpack4(v[k]);
                 }
                 M = m;
             }
@@ -1570,6 +1590,7 @@ struct AttnPlan {
         int nwg;              // persistent workgroups
         int spb;              // fixed units per workgroup (0: equal shares)
         bool whole;           // one workgroup per pair
+        bool slot_f32;        // the partial outputs are fp32
         int rows_lo, rows_hi; // requests with Hq/Hkv * n_i in [rows_lo, rows_hi]
         int64_t slots;        // partial slots
         size_t off;           // workspace offset of the class's arrays
@@ -1683,9 +1704,9 @@ bool with_shape(int d, int nw, int tpw, F&& f) {
     return false;
 }
 
-template <typename S, bool APPEND = false>
+template <typename S, bool APPEND = false, typename Slot = uint16_t>
 constexpr auto persist_kernel() {
-    return attn_persist<S::D, S::NW, S::TPW, S::NS, APPEND>;
+    return attn_persist<S::D, S::NW, S::TPW, S::NS, APPEND, Slot>;
 }
 
 int validate(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
@@ -1792,6 +1813,7 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
         const int64_t all = (int64_t)device_cus() * res, ranges = ranges_per_pair(nb_max, pairs, all);
         const int64_t apart = std::max<int64_t>(2, (nb_max + ranges - 1) / ranges);
         const int64_t resident = std::min(all, (units_max + apart - 1) / apart);
+        c.slot_f32 = resident < all;
         const int64_t mult = std::min<int64_t>(8, std::max<int64_t>(1, units_max / resident / kOversubUnits));
         c.nwg = (int)(resident * mult);
     }
@@ -1800,9 +1822,10 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
         c.whole = true;
         c.nwg = (int)pairs;
         c.slots = 0;
+        c.slot_f32 = false;
     }
     c.unit_bytes = align_up(sizeof(int32_t) * ((size_t)std::max(1, p->num_seqs) + 1), 256);
-    c.slot_o_bytes = align_up((size_t)c.slots * per * p->head_dim * sizeof(uint16_t), 256);
+    c.slot_o_bytes = align_up((size_t)c.slots * per * p->head_dim * (c.slot_f32 ? sizeof(float) : sizeof(uint16_t)), 256);
     c.slot_lse_bytes = align_up((size_t)c.slots * per * sizeof(float), 256);
     return VERIFY_OK;
 }
@@ -1893,22 +1916,23 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
         if (!a.inline_sched && !a.whole)
             hipLaunchKernelGGL((attn_schedule<S::D>), dim3(1), dim3(1024), 0, stream, a, m.q_start,
                                m.seq_lens, m.unit_start, m.out);
-        if (m.k_new)
-            hipLaunchKernelGGL((persist_kernel<S, true>()), dim3(a.nwg), dim3(S::NW * kWave), 0, stream,
-                               a, m.q, m.kc, m.vc, m.block_tables, m.seq_lens, m.q_start, m.unit_start,
-                               m.out, m.slot_o, m.slot_lse, m.k_new, m.v_new);
-        else
-            hipLaunchKernelGGL(persist_kernel<S>(), dim3(a.nwg), dim3(S::NW * kWave), 0, stream, a,
-                               m.q, m.kc, m.vc, m.block_tables, m.seq_lens, m.q_start, m.unit_start,
-                               m.out, m.slot_o, m.slot_lse, nullptr, nullptr);
+        auto walk = [&](auto append, auto slot) {
+            using Slot = decltype(slot);
+            hipLaunchKernelGGL((persist_kernel<S, decltype(append)::value, Slot>()), dim3(a.nwg),
+                               dim3(S::NW * kWave), 0, stream, a, m.q, m.kc, m.vc, m.block_tables, m.seq_lens,
+                               m.q_start, m.unit_start, m.out, static_cast<Slot*>(m.slot_o), m.slot_lse, m.k_new,
+                               m.v_new);
+        };
+        if (m.k_new) pl.slot_f32 ? walk(std::true_type{}, float{}) : walk(std::true_type{}, uint16_t{});
+        else pl.slot_f32 ? walk(std::false_type{}, float{}) : walk(std::false_type{}, uint16_t{});
         if (a.whole) return;
         const int64_t pairs = (int64_t)a.num_seqs * a.hkv * a.rg_max;
         // rows of a row group: at most rows_per_group, at most G * max_q_len
         const int group_rows = std::max(1, std::min(a.rows_per_group, max_rows));
-        auto combine = [&](auto sg) {
+        auto combine = [&](auto sg, auto four) {
             constexpr int SG = decltype(sg)::value, RPB = kCombineThreads / (S::D / 4) / SG;
             const unsigned chunks = (unsigned)((group_rows + RPB - 1) / RPB);
-            hipLaunchKernelGGL((attn_combine_slots<S::D, SG>), dim3((unsigned)pairs, chunks),
+            hipLaunchKernelGGL((attn_combine_slots<S::D, SG, decltype(four)>), dim3((unsigned)pairs, chunks),
                                dim3(kCombineThreads), 0, stream, a, m.seq_lens, m.q_start,
                                m.unit_start, m.slot_o, m.slot_lse, m.out);
         };
@@ -1918,9 +1942,11 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
         // rows in 14 slots 26.5 -> 23.0 us, but 41 pairs of 240 rows in 12 slots 30.2
         // -> 34.7, 30 pairs of 88 rows in 10 slots 36.2 -> 38.6)
         const int64_t wgs4 = pairs * ((group_rows * S::D + kCombineThreads - 1) / kCombineThreads);
-        if (2 * (int64_t)a.nwg > 3 * kCombineSlots * pairs && wgs4 <= 8 * (int64_t)device_cus())
-            combine(std::integral_constant<int, 4>{});
-        else combine(std::integral_constant<int, 1>{});
+        const std::integral_constant<int, 1> alone;
+        const std::integral_constant<int, 4> shared;
+        const bool share = 2 * (int64_t)a.nwg > 3 * kCombineSlots * pairs && wgs4 <= 8 * (int64_t)device_cus();
+        if (pl.slot_f32) share ? combine(shared, f32x4_t{}) : combine(alone, f32x4_t{});
+        else share ? combine(shared, uint2{}) : combine(alone, uint2{});
     });
 }
 
@@ -2022,7 +2048,7 @@ int attention_call(const verify_attn_params* params, int32_t total_q, int32_t ma
             const AttnPlan::Class& c = pl.cls[k];
             char* ws = static_cast<char*>(workspace) + c.off;
             m.unit_start = reinterpret_cast<int32_t*>(ws);
-            m.slot_o = reinterpret_cast<uint16_t*>(ws + c.unit_bytes);
+            m.slot_o = ws + c.unit_bytes;
             m.slot_lse = reinterpret_cast<float*>(ws + c.unit_bytes + c.slot_o_bytes);
             a.rows_per_group = c.nw * c.tpw * 16;
             a.rg_max = c.rg_max;

@@ -111,3 +111,25 @@ def test_walk_rows_past_max_q_len(hq, hkv, d, window):
     assert (local >= reach).any()
     assert_attention_close(out[local < reach], ref[local < reach], "bf16", "reached")
     assert np.isnan(out[local >= reach]).all()
+
+
+@pytest.mark.parametrize("hq,hkv,d,contexts,drafts", [
+    (32, 8, 128, [1500], [4]), (32, 8, 128, [500], [4]), (64, 8, 64, [3100], [8]), (8, 1, 128, [900, 333], [4, 16]),
+])
+def test_walk_of_few_pairs_rounds_twice(hq, hkv, d, contexts, drafts):
+    """Few pairs, cut into ranges that do not fill the chip: only the weights and
+    the output are rounded to bf16, the partial outputs are not.  A rounding to
+    bf16 has a relative error of 2^-7 / sqrt(12) / m for a mantissa m, 1.6e-3 in the
+    root mean square over [1, 2): 2.26e-3 for two of them, 2.76e-3 for three.  The
+    line lies between."""
+    p = random_paged(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, dtype="bf16", contexts=contexts, drafts=drafts,
+                     seed=hq + d)
+    t = lambda a: torch.as_tensor(a, device=DEV)
+    q, kc, vc = p.q.to(DEV), p.k_cache.to(DEV), p.v_cache.to(DEV)
+    kw = dict(max_q_len=int(np.diff(p.q_start).max()), max_seq_len=int(p.seq_lens.max()))
+    assert av.attention_plan(q, kc, t(p.block_tables), **kw)["units_per_workgroup"] == 0
+    out = to_host_f64(gpu_attention(q, kc, vc, t(p.block_tables), t(p.seq_lens), t(p.q_start), **kw))
+    ref = oracle.attention(**p.oracle_args())
+    err = np.linalg.norm(out - ref) / np.linalg.norm(ref)
+    print("two roundings", hq, hkv, d, contexts, "error %.3e" % err, file=sys.stderr, flush=True)
+    assert err < 2.5e-3
