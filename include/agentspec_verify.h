@@ -135,8 +135,9 @@ typedef struct verify_attn_params {
  *                computed: their outputs are written as quiet NaN.
  *   workspace    device scratch of at least the size returned by
  *                verify_attention_workspace_size() for the same (params,
- *                total_q, max_q_len, max_seq_len); may be NULL if that size is
- *                0.  Its contents on entry are ignored.
+ *                total_q, max_q_len, max_seq_len), or for those of a batch of
+ *                more requests and rows with the same other arguments; may be
+ *                NULL if that size is 0.  Its contents on entry are ignored.
  */
 int verify_attention_workspace_size(const verify_attn_params *params, int32_t total_q,
                                     int32_t max_q_len, int32_t max_seq_len, size_t *bytes);

@@ -1595,10 +1595,16 @@ struct AttnPlan {
         int64_t slots;        // partial slots
         size_t off;           // workspace offset of the class's arrays
         size_t unit_bytes, slot_o_bytes, slot_lse_bytes;
+        size_t cover_bytes;   // what the class needs at most with fewer requests
     };
     int nclass;
     Class cls[2];
-    size_t total_bytes;
+    size_t total_bytes;       // workspace of the call
+    // workspace that the size query returns: enough for any call of fewer
+    // requests too.  A caller keeps one workspace for its largest batch, and a
+    // smaller one can need more of it: its pairs are cut where those of the
+    // largest fill the chip whole, and into more ranges.
+    size_t cover_bytes;
 };
 
 // Batches whose requests carry up to this many query rows per KV head (three
@@ -1800,6 +1806,7 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
     const int64_t units_max = pairs * nb_max;
     if (units_max >= (int64_t)1 << 31) return VERIFY_EUNSUPPORTED;
     c.spb = p->kv_split_blocks;
+    int64_t all = 0;  // resident workgroups
     if (c.spb > 0) {
         c.nwg = (int)std::min<int64_t>((units_max + c.spb - 1) / c.spb, (int64_t)1 << 30);
     } else {
@@ -1810,7 +1817,8 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
                 res = append ? resident_wgs<decltype(sh), true>() : resident_wgs<decltype(sh)>();
             }))
             return VERIFY_EUNSUPPORTED;
-        const int64_t all = (int64_t)device_cus() * res, ranges = ranges_per_pair(nb_max, pairs, all);
+        all = (int64_t)device_cus() * res;
+        const int64_t ranges = ranges_per_pair(nb_max, pairs, all);
         const int64_t apart = std::max<int64_t>(2, (nb_max + ranges - 1) / ranges);
         const int64_t resident = std::min(all, (units_max + apart - 1) / apart);
         c.slot_f32 = resident < all;
@@ -1818,6 +1826,13 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
         c.nwg = (int)(resident * mult);
     }
     c.slots = pairs + c.nwg;
+    // slots with fewer requests: no more pairs and workgroups than these (nwg
+    // before it is capped by the units), fp32 only in launches of fewer than `all`
+    int64_t most = c.slots, most_f32 = 0;
+    if (c.spb == 0) {
+        most = pairs + std::min(8 * all, std::max(all, units_max / kOversubUnits));
+        most_f32 = std::min(pairs, all) + all;
+    }
     if (c.spb == 0 && whole_pairs(nb_max, std::min(pairs, active), device_cus(), c.nw, c.tpw)) {
         c.whole = true;
         c.nwg = (int)pairs;
@@ -1827,6 +1842,9 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
     c.unit_bytes = align_up(sizeof(int32_t) * ((size_t)std::max(1, p->num_seqs) + 1), 256);
     c.slot_o_bytes = align_up((size_t)c.slots * per * p->head_dim * (c.slot_f32 ? sizeof(float) : sizeof(uint16_t)), 256);
     c.slot_lse_bytes = align_up((size_t)c.slots * per * sizeof(float), 256);
+    const size_t values = (size_t)per * p->head_dim;
+    c.cover_bytes = c.unit_bytes + align_up(std::max(most * values * sizeof(uint16_t), most_f32 * values * sizeof(float)), 256) +
+                    align_up((size_t)std::max(most, most_f32) * per * sizeof(float), 256);
     return VERIFY_OK;
 }
 
@@ -1837,8 +1855,9 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
 // them (a workgroup per compute unit), down to a block per wavefront: one request
 // of 94 blocks 28 us at 32, under the call's host time from 16 down; two requests
 // of 3750 blocks on one KV head 63 / 45 / 38 / 39 / 56 us at 8 / 16 / 24 / 32 / 64.
-// From 262144 blocks on the items are held to about 8192.
+// From 262144 blocks on the items are held to about kF32MostItems.
 constexpr int kF32Items = 256;
+constexpr int kF32MostItems = 8192;
 constexpr int kF32SplitBlocks = 32;
 
 int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
@@ -1877,6 +1896,7 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
             AttnPlan::Class& c = pl.cls[k];
             c.off = off;
             off += c.unit_bytes + c.slot_o_bytes + c.slot_lse_bytes;
+            pl.cover_bytes += c.cover_bytes;
         }
         pl.total_bytes = off;
     } else {
@@ -1888,7 +1908,7 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
         if (sb == 0) {
             const int64_t total = (int64_t)std::max(1, p->num_seqs) * p->num_kv_heads * pl.row_groups * nb_max;
             int64_t want = ((total + kF32Items - 1) / kF32Items + 3) / 4 * 4;
-            want = std::min<int64_t>(want, std::max<int64_t>(kF32SplitBlocks, (total / 8192 + 3) / 4 * 4));
+            want = std::min<int64_t>(want, std::max<int64_t>(kF32SplitBlocks, (total / kF32MostItems + 3) / 4 * 4));
             sb = (int)std::min<int64_t>(want, nb_max);
         }
         pl.split_blocks = std::max(1, sb);
@@ -1902,6 +1922,23 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
             pl.part_lse_bytes = align_up(items * sizeof(float), 256);
         }
         pl.total_bytes = pl.part_o_bytes + pl.part_lse_bytes;
+        pl.cover_bytes = pl.total_bytes;
+        if (p->kv_split_blocks == 0 && nb_max > 4) {
+            // (rows, splits) of b requests, over all b: rows t <= total_q and t <= b
+            // max_q_len.  A split has at least total / kF32Items blocks (total is
+            // proportional to b), or kF32SplitBlocks and total / kF32MostItems of
+            // which rounding down takes less than one in 33, so t * splits is at
+            // most t + max_q_len * items / (KV heads * row groups).
+            const int64_t t = total_q, walks = (int64_t)p->num_kv_heads * pl.row_groups;
+            auto most = [&](int64_t items, int64_t blocks) {
+                return std::min(t * ((nb_max + blocks - 1) / blocks),
+                                t + ((int64_t)std::max(1, max_q_len) * items + walks - 1) / walks);
+            };
+            const size_t rows_splits = (size_t)std::max(most(kF32Items, 4), most(kF32MostItems * 33 / 32, kF32SplitBlocks));
+            const size_t part = rows_splits * p->num_q_heads;
+            pl.cover_bytes = std::max(pl.total_bytes, align_up(part * p->head_dim * sizeof(float), 256) +
+                                                          align_up(part * sizeof(float), 256));
+        }
     }
     *out = pl;
     return VERIFY_OK;
@@ -1990,7 +2027,7 @@ extern "C" int verify_attention_workspace_size(const verify_attn_params* params,
     rc = make_plan(params, total_q, max_q_len, max_seq_len, &pl);
     if (rc == VERIFY_OK) rc = make_plan(params, total_q, max_q_len, max_seq_len, &pla, true);
     if (rc != VERIFY_OK) return rc;
-    *bytes = std::max(pl.total_bytes, pla.total_bytes);
+    *bytes = std::max(pl.cover_bytes, pla.cover_bytes);
     return VERIFY_OK;
 }
 

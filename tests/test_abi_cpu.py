@@ -487,3 +487,26 @@ def test_attention_plan_whole_pairs_are_safe_for_uneven_lengths():
     # two row classes of 64 requests: all can be long, or (62 rows of four, two of 17) 23 of them
     assert units(63, 16, 64) == [-1, -1]
     assert units(63, 16, 64, total_q=62 * 4 + 2 * 17) == [-1, 0]
+
+
+@pytest.mark.parametrize("dtype", [av.BF16, av.F32])
+@pytest.mark.parametrize("kw, rows, tokens", [
+    (dict(), 5, 600), (dict(), 5, 1500), (dict(), 9, 40000), (dict(), 17, 1000), (dict(), 33, 131072),
+    (dict(num_q_heads=8, num_kv_heads=1), 5, 1500), (dict(sliding_window=512), 5, 16384),
+    (dict(num_q_heads=64, head_dim=64, sliding_window=128), 9, 16384), (dict(num_q_heads=64, head_dim=64), 9, 900),
+    (dict(num_kv_heads=2, num_q_heads=2), 3, 94 * 16), (dict(kv_split_blocks=7), 5, 3000),
+])
+def test_attention_workspace_covers_smaller_batches(dtype, kw, rows, tokens):
+    """A caller keeps one workspace for its largest batch: no batch of fewer
+    requests asks for more.  (That a call's own need stays within what is asked
+    for is tested on the GPU.)"""
+    def size(requests, total_q):
+        p = _params(dtype=dtype, num_seqs=requests, max_blocks_per_seq=(tokens + 15) // 16, **kw)
+        rc, n = _ws(p, total_q=total_q, max_q=rows, max_s=tokens)
+        assert rc == 0
+        return n
+
+    batches = list(range(1, 70)) + [96, 127, 128, 200, 256, 300]
+    sizes = [size(b, b * rows) for b in batches]
+    assert sizes == sorted(sizes)
+    assert all(size(b, b) <= n for b, n in zip(batches, sizes))

@@ -133,3 +133,28 @@ def test_walk_of_few_pairs_rounds_twice(hq, hkv, d, contexts, drafts):
     err = np.linalg.norm(out - ref) / np.linalg.norm(ref)
     print("two roundings", hq, hkv, d, contexts, "error %.3e" % err, file=sys.stderr, flush=True)
     assert err < 2.5e-3
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("hq,hkv,d,tokens,draft,window", [
+    (32, 8, 128, 600, 4, 0), (8, 2, 64, 900, 8, 0), (8, 2, 128, 1500, 4, 512), (8, 1, 128, 2500, 16, 0),
+])
+def test_one_workspace_for_every_batch(dtype, hq, hkv, d, tokens, draft, window):
+    """The workspace asked for the largest batch serves the smaller ones, whose
+    pairs are cut where those of the largest are walked whole (bf16), or into more
+    splits (fp32); nothing past its end is written."""
+    B = 64
+    p = random_paged(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, dtype=dtype,
+                     contexts=[tokens - 7 * (i % 5) for i in range(B)], drafts=[draft] * B, window=window, seed=d + hkv)
+    t = lambda a: torch.as_tensor(a, device=DEV)
+    q, kc, vc, bt = p.q.to(DEV), p.k_cache.to(DEV), p.v_cache.to(DEV), t(p.block_tables)
+    kw = dict(max_q_len=draft + 1, max_seq_len=int(p.seq_lens.max()), sliding_window=window)
+    n = av.attention_workspace_size(q, kc, bt, **kw)
+    raw = torch.full((n + 4096,), 0xC3, dtype=torch.uint8, device=DEV)
+    for b in (1, 2, 3, 5, 8, 13, 16, 20, 31, 40, 63, 64):
+        print("one workspace", dtype, hkv, d, b, file=sys.stderr, flush=True)
+        rows = b * (draft + 1)
+        args = (q[:rows], kc, vc, bt[:b].contiguous(), t(p.seq_lens[:b]), t(p.q_start[:b + 1]))
+        out = av.verify_attention(*args, workspace=raw[:n], **kw)
+        assert torch.equal(out, av.verify_attention(*args, **kw))
+        assert bool((raw[n:] == 0xC3).all())
