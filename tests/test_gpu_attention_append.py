@@ -118,7 +118,8 @@ def test_fused_append_row_classes():
 
 
 def test_fused_append_scheduled_batch():
-    """300 requests: the separate schedule launch runs first."""
+    """300 requests: short pairs are walked whole, and with a fixed split the
+    separate schedule launch runs first."""
     rng = np.random.default_rng(8)
     say("attention append 300 requests")
     p = random_paged(num_q_heads=32, num_kv_heads=8, head_dim=128, dtype="bf16",
@@ -126,6 +127,23 @@ def test_fused_append_scheduled_batch():
                      drafts=list(rng.integers(0, 9, size=300)), seed=22)
     _case(p, split=0, what="300 requests")
     _case(p, split=4, what="300 requests split 4")
+
+
+@pytest.mark.parametrize("hq,hkv,d,longest,drafts,classes", [(8, 1, 128, 2100, 5, 1), (32, 4, 128, 1900, 21, 2),
+                                                             (16, 2, 64, 2100, 9, 1)])
+def test_fused_append_scheduled_in_equal_shares(hq, hkv, d, longest, drafts, classes):
+    """257 requests, one of them long: the separate schedule launch runs first
+    and the pairs are cut into equal shares, in one and in two row classes."""
+    rng = np.random.default_rng(9 + d)
+    contexts, k = rng.integers(0, 100, size=257), rng.integers(0, drafts, size=257)
+    contexts[128], k[128] = longest, drafts - 1
+    say("attention append scheduled in equal shares", hq, hkv, d)
+    p = random_paged(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, dtype="bf16", contexts=contexts.tolist(),
+                     drafts=k.tolist(), seed=23)
+    plan = av.attention_plan(p.q, p.k_cache, torch.as_tensor(p.block_tables),
+                             max_q_len=int(np.diff(p.q_start).max()), max_seq_len=int(p.seq_lens.max()))
+    assert [c["units_per_workgroup"] for c in plan["classes"]] == [0] * classes
+    _case(p, split=0, what="257 requests, one long")
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

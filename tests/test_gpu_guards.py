@@ -148,16 +148,20 @@ def test_attention_guards(case):
         assert bool(torch.isnan(outputs["out"][0].float()).any())
 
 
-def test_attention_guards_scheduled_batch():
-    """300 requests: above the inline schedule, so a separate schedule launch
-    writes the unit table into the workspace first."""
+@pytest.mark.parametrize("longest,units", [(399, -1), (2100, 0)], ids=["whole pairs", "equal shares"])
+def test_attention_guards_scheduled_batch(longest, units):
+    """300 requests, above the inline schedule: with a long context among them a
+    separate schedule launch writes the unit table into the workspace first; the
+    pairs of short contexts are walked whole, without it."""
     rng = np.random.default_rng(5)
     contexts = list(rng.integers(0, 400, size=300))
+    contexts[150] = longest
     drafts = list(rng.integers(0, 9, size=300))
-    say("guards attention 300 requests")
+    say("guards attention 300 requests", longest)
     p = random_paged(num_q_heads=32, num_kv_heads=8, head_dim=128, dtype="bf16", contexts=contexts,
                      drafts=drafts, seed=12)
     call, arena, inputs, outputs, plan = _attention_case(p)
+    assert plan["units_per_workgroup"] == units
     _twice(call, arena, inputs, outputs, "attention 300 requests")
 
 

@@ -279,6 +279,7 @@ def test_attention_requests_without_rows(dtype, hq, hkv, d):
 def test_attention_batches_above_the_inline_schedule(dtype, hq, hkv, d):
     # more than 256 requests: the per-request unit offsets come from the
     # separate one-workgroup schedule launch instead of each workgroup's scan
+    # (with fixed splits; the automatic ones give these short pairs whole)
     rng = np.random.default_rng(300 + d)
     B = 300
     contexts = rng.integers(0, 200, size=B)
@@ -291,11 +292,35 @@ def test_attention_batches_above_the_inline_schedule(dtype, hq, hkv, d):
         _check_paged(p, split=split, what="300 requests split=%d" % split)
 
 
+@pytest.mark.parametrize("hq,hkv,d,longest,drafts,classes", [
+    (8, 1, 128, 2100, 5, 1), (8, 2, 64, 2100, 9, 1), (4, 1, 128, 3000, 1, 1), (32, 4, 128, 1900, 21, 2),
+])
+@pytest.mark.parametrize("B", [257, 300])
+def test_attention_separate_schedule_in_equal_shares(hq, hkv, d, longest, drafts, classes, B):
+    # the separate schedule launch where its ranges are equal shares and a long
+    # context among short ones keeps pairs from being given whole: unit offsets,
+    # ranges and merge are read from the workspace
+    rng = np.random.default_rng(B + d + longest)
+    contexts = rng.integers(0, 100, size=B)
+    contexts[B // 2] = longest
+    k = rng.integers(0, drafts, size=B)
+    k[::41] = -1
+    k[B // 2] = drafts - 1
+    say("attn separate schedule, equal shares", hq, hkv, d, B)
+    p = random_paged(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, dtype="bf16",
+                     contexts=contexts.tolist(), drafts=k.tolist(), seed=int(d + B))
+    dv = _to_dev(p)
+    plan = av.attention_plan(dv["q"], dv["kc"], dv["bt"], max_q_len=int(np.diff(p.q_start).max()),
+                             max_seq_len=int(p.seq_lens.max()))
+    assert [c["units_per_workgroup"] for c in plan["classes"]] == [0] * classes
+    _check_paged(p, split=0, what="separate schedule %d requests" % B)
+
+
 @pytest.mark.parametrize("window,with_sinks", [(0, False), (40, True)])
 def test_attention_batches_above_the_inline_schedule_in_row_classes(window, with_sinks):
     # more than 256 requests with draft lengths on both sides of the row-class
-    # boundary: two launches, each with its own schedule launch and merge,
-    # with a sliding window and sinks in one case
+    # boundary: two launches, with fixed splits each with its own schedule
+    # launch and merge, with a sliding window and sinks in one case
     rng = np.random.default_rng(301 + window)
     B = 300
     contexts = rng.integers(0, 200, size=B)

@@ -158,3 +158,26 @@ def test_one_workspace_for_every_batch(dtype, hq, hkv, d, tokens, draft, window)
         out = av.verify_attention(*args, workspace=raw[:n], **kw)
         assert torch.equal(out, av.verify_attention(*args, **kw))
         assert bool((raw[n:] == 0xC3).all())
+
+
+@pytest.mark.parametrize("hq,hkv,d,contexts,drafts,bound,ranges", [
+    (32, 8, 128, [40, 100, 5, 0, 63], [4, 0, 8, 2, 1], 16384, 500),  # fewer blocks than workgroups: ranges of one
+    (64, 8, 64, [40, 100, 5, 0, 63], [4, 0, 8, 2, 1], 16384, 500),
+    (8, 1, 128, [16000], [4], 16384, 80),                             # three rounds of the shared-row merge
+    (8, 2, 64, [12000, 17], [8, 0], 16384, 80),
+])
+def test_walk_ranges(hq, hkv, d, contexts, drafts, bound, ranges):
+    """A loose max_seq_len, whose plan has more workgroups than there are blocks,
+    and long pairs cut into more slots than a round of the merge reads."""
+    p = random_paged(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, dtype="bf16", contexts=contexts, drafts=drafts,
+                     seed=hq + d + len(contexts))
+    t = lambda a: torch.as_tensor(a, device=DEV)
+    q, kc, vc = p.q.to(DEV), p.k_cache.to(DEV), p.v_cache.to(DEV)
+    kw = dict(max_q_len=int(np.diff(p.q_start).max()), max_seq_len=bound)
+    print("walk ranges", hq, hkv, d, contexts, file=sys.stderr, flush=True)
+    plan = av.attention_plan(q, kc, t(p.block_tables), **kw)
+    assert plan["units_per_workgroup"] == 0 and plan["workgroups"] >= ranges
+    if len(contexts) > 2:
+        assert plan["workgroups"] > hkv * ((p.seq_lens + 15) // 16).sum()
+    out = gpu_attention(q, kc, vc, t(p.block_tables), t(p.seq_lens), t(p.q_start), **kw)
+    assert_attention_close(to_host_f64(out), oracle.attention(**p.oracle_args()), "bf16", "walk ranges")
