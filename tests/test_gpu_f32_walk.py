@@ -74,3 +74,25 @@ def test_f32_walk_edges(case, unmapped):
     if not unmapped:
         assert np.array_equal(workload.host_storage(kc2), workload.host_storage(kc))
         assert np.array_equal(workload.host_storage(vc2), workload.host_storage(vc))
+
+
+@pytest.mark.parametrize("hq,hkv,d,contexts,draft,window", [
+    (1, 1, 64, [3434 + 900 * i for i in range(12)], 2, 128), (2, 2, 128, [229, 600, 900, 1220], 3, 0),
+    (16, 4, 64, [1500, 700], 4, 0),
+])
+def test_f32_splits_lose_nothing(hq, hkv, d, contexts, draft, window):
+    """Cutting a request into splits adds to its error against 64 bits only the
+    merge's own sums, a few per cent beside the scores': no split's weight goes
+    through a logarithm of the size of the scores (that added an eighth)."""
+    p = random_paged(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, dtype="f32", contexts=contexts,
+                     drafts=[draft] * len(contexts), window=window, seed=hq + d)
+    t = lambda a: torch.as_tensor(a, device=DEV)
+    args = (p.q.to(DEV), p.k_cache.to(DEV), p.v_cache.to(DEV), t(p.block_tables), t(p.seq_lens), t(p.q_start))
+    kw = dict(max_q_len=draft + 1, max_seq_len=int(p.seq_lens.max()), window=window)
+    ref = oracle.attention(**p.oracle_args())
+    err = {}
+    for split in (0, 1, 100000):
+        out = to_host_f64(gpu_attention(*args, split=split, **kw))
+        err[split] = np.linalg.norm(out - ref) / np.linalg.norm(ref)
+    print("f32 splits", hq, hkv, d, window, err, file=sys.stderr, flush=True)
+    assert err[0] <= 1.05 * err[100000] and err[1] <= 1.05 * err[100000]
