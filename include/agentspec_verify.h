@@ -166,8 +166,10 @@ int verify_attention(const verify_attn_params *params, int32_t total_q, int32_t 
  *   all other arguments and the workspace as for verify_attention (the size
  *   that verify_attention_workspace_size returns covers both calls).
  * Under verify_attention's bounds (S_i <= max_seq_len <= 16 *
- * max_blocks_per_seq), out and the cache equal, bit for bit, what
- * verify_kv_append followed by verify_attention on the same stream writes.
+ * max_blocks_per_seq), the cache equals, bit for bit, what verify_kv_append
+ * followed by verify_attention on the same stream writes.  So does out in fp32
+ * and with kv_split_blocks > 0; otherwise it may differ from it by rounding
+ * where the two kernels' launches cut the walk differently.
  * k_new / v_new must not overlap the caches.
  */
 int verify_attention_append(const verify_attn_params *params, int32_t total_q, int32_t max_q_len,
@@ -453,7 +455,9 @@ int verify_check_batch(int32_t num_seqs, int32_t total_q, int32_t max_q_len,
 /* Static, human-readable name of a status code. */
 const char *verify_status_string(int status);
 
-/* Library ABI version (major * 10000 + minor * 100 + patch). */
+/* Library ABI version (major * 10000 + minor * 100 + patch): 1.9.0.  Since 1.9.0
+ * verify_attention_plan reports whole pairs (-1), and the size that
+ * verify_attention_workspace_size returns covers batches of fewer requests. */
 int verify_abi_version(void);
 
 #ifdef __cplusplus

@@ -10,8 +10,9 @@
 // work item; its wavefronts take the split's blocks round-robin, each keeps an
 // online-softmax state (running max, running sum, unnormalised output) per row,
 // and the four states are merged through LDS at the end.  A request whose keys
-// fit one split writes its output directly; otherwise every split writes a
-// normalised partial output and its log-sum-exp, and attn_combine merges them.
+// fit one split writes its output directly; otherwise every split writes its
+// partial output, maximum and sum, and attn_combine merges them.  (This is the
+// fp32 kernel's; the bf16 walk below cuts the work in its own way.)
 //
 // Masks.  Row j of request i sits at position p = S_i - n_i + j and sees keys
 // t <= p, and with a sliding window W only t > p - W; the walk covers the
@@ -1920,8 +1921,9 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
         }
         pl.split_blocks = std::max(1, sb);
         pl.max_splits = (int)((nb_max + pl.split_blocks - 1) / pl.split_blocks);
-        // grid (splits, KV heads x row groups, requests): y is a 16-bit dimension,
-        // and the call's limit is eight rows per row group
+        // the call's limit since its grid had a 16-bit dimension of row groups of
+        // eight rows; the walk's (pairs x splits, requests) needs fewer than 2^24
+        // pairs, which it implies
         if ((int64_t)p->num_kv_heads * ((rows + 7) / 8) > 65535) return VERIFY_EUNSUPPORTED;
         if (pl.max_splits > 1) {
             const size_t items = (size_t)total_q * p->num_q_heads * pl.max_splits;
@@ -1981,8 +1983,8 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
                                m.unit_start, m.slot_o, m.slot_lse, m.out);
         };
         if (pairs <= 0) return;
-        // more than one and a half rounds of slots per pair: four thread groups share
-        // a row, if the four times larger grid is resident at once (88 pairs of 52
+        // more than one and a half rounds of slots per planned pair (the average; a
+        // long pair among short ones has more): four thread groups share a row, if the four times larger grid is resident at once (88 pairs of 52
         // rows in 14 slots 26.5 -> 23.0 us, but 41 pairs of 240 rows in 12 slots 30.2
         // -> 34.7, 30 pairs of 88 rows in 10 slots 36.2 -> 38.6)
         const int64_t wgs4 = pairs * ((group_rows * S::D + kCombineThreads - 1) / kCombineThreads);

@@ -40,7 +40,7 @@ def test_library_exports_every_declared_symbol():
     lib = av.library()
     for name in declared_symbols():
         assert hasattr(lib, name), name
-    assert av.abi_version() == 10800
+    assert av.abi_version() == 10900
     assert lib.verify_status_string(0) == b"ok"
     assert lib.verify_status_string(-3) == b"workspace too small"
 
@@ -111,8 +111,8 @@ def test_attention_argument_validation(kw, want):
 
 def test_attention_workspace_query_and_checks():
     lib = av.library()
-    # fp32 (split-K VALU path): 63 blocks / 8 per split -> 8 splits of fp32
-    # partial outputs and log-sum-exps; a single split needs no workspace
+    # fp32 (split-K path): 63 blocks / 8 per split -> 8 splits of fp32
+    # partial outputs, maxima and sums; a single split needs no workspace
     rc, n = _ws(_params(dtype=av.F32, kv_split_blocks=8), total_q=36, max_q=9, max_s=1000)
     assert rc == 0 and n >= 36 * 32 * 8 * (128 + 1) * 4
     rc, n1 = _ws(_params(dtype=av.F32, kv_split_blocks=1000), total_q=36, max_q=9, max_s=1000)
