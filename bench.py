@@ -156,7 +156,8 @@ def summarize_pmc(fetch_csv: str, write_csv: str, workload: str) -> None:
         raise SystemExit("no calibration dispatch (run bench.py with --copy-calibration)")
     ff = CALIB_BYTES / (fcal * 1024.0)
     wf = CALIB_BYTES / (wcal * 1024.0)
-    attn = [k for k in fk if k.split("<")[0].split(" ")[0] in call_kernels and ",true>" not in k]
+    attn = [k for k in fk if k.split("<")[0].split(" ")[0] in call_kernels
+            and not re.search(",true[,>]", k)]
     total = 0.0
     lines = []
     for k in sorted(attn):
@@ -515,7 +516,8 @@ def summarize_trace(csv_path: str, layers: int) -> None:
     """Inter-kernel idle time inside the timed verify steps, from the kernel
     trace of a rocprofv3 --kernel-trace run of bench.py.  A step is a run of
     attention kernels (per layer and row class: attn_schedule for large
-    batches, attn_persist, attn_combine_slots; at least two per layer) ended by
+    batches, attn_persist, attn_combine_slots unless pairs are walked whole; at
+    least one per layer) ended by
     argmax_chunks, accept_scan, issued back to back.  The most frequent such
     kernel sequence is the step (the timed steps and the warm-up steps have
     it; the attention-only calls timed after them do not)."""
@@ -537,7 +539,7 @@ def summarize_trace(csv_path: str, layers: int) -> None:
             k = j
             while k > 0 and names[k - 1] in attention:
                 k -= 1
-            if j - k >= 2 * layers:
+            if j - k >= layers:
                 found.append((k, j + 2))
     if not found:
         raise SystemExit("no verify step found in %s" % csv_path)

@@ -1294,13 +1294,14 @@ __device__ __forceinline__ f32x4_t unpack4(const uint2& v) {
 }
 __device__ __forceinline__ f32x4_t unpack4(const f32x4_t& v) { return v; }
 
-// Four: what holds four partial values (uint2 or f32x4_t).
-template <int D, int SG, typename Four>
-__global__ __launch_bounds__(kCombineThreads) __attribute__((amdgpu_waves_per_eu(sizeof(Four) == 8 ? 8 : 5)))
+// Slot: the type of the partial outputs, as in attn_persist.
+template <int D, int SG, typename Slot>
+__global__ __launch_bounds__(kCombineThreads) __attribute__((amdgpu_waves_per_eu(sizeof(Slot) == 2 ? 8 : 5)))
 void attn_combine_slots(
     PArgs a, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_start,
-    const int32_t* __restrict__ unit_start, const void* __restrict__ slot_o,
+    const int32_t* __restrict__ unit_start, const Slot* __restrict__ slot_o,
     const float* __restrict__ slot_lse, uint16_t* __restrict__ out) {
+    using Four = std::conditional_t<sizeof(Slot) == 2, uint2, f32x4_t>;  // four partial values
     constexpr int QUADS = D / 4;                       // 4-dim vectors per row
     constexpr int RPB = kCombineThreads / QUADS / SG;  // rows per workgroup
     const int P = blockIdx.x;
@@ -1350,7 +1351,7 @@ void attn_combine_slots(
                 for (int k = 0; k < kCombineSlots; ++k) {
                     const int64_t sl = slot0 + min(s0 + k, ns - 1);
                     lse[k] = slot_lse[sl * ROWS + lr];
-                    v[k] = static_cast<const Four*>(slot_o)[slot_o_index<D>(sl, ROWS, lr, d0) / 4];
+                    v[k] = *reinterpret_cast<const Four*>(slot_o + slot_o_index<D>(sl, ROWS, lr, d0));
                 }
 #pragma unroll
                 for (int k = 0; k < kCombineSlots; ++k) {
@@ -1975,12 +1976,13 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
         const int64_t pairs = (int64_t)a.num_seqs * a.hkv * a.rg_max;
         // rows of a row group: at most rows_per_group, at most G * max_q_len
         const int group_rows = std::max(1, std::min(a.rows_per_group, max_rows));
-        auto combine = [&](auto sg, auto four) {
+        auto combine = [&](auto sg, auto slot) {
+            using Slot = decltype(slot);
             constexpr int SG = decltype(sg)::value, RPB = kCombineThreads / (S::D / 4) / SG;
             const unsigned chunks = (unsigned)((group_rows + RPB - 1) / RPB);
-            hipLaunchKernelGGL((attn_combine_slots<S::D, SG, decltype(four)>), dim3((unsigned)pairs, chunks),
+            hipLaunchKernelGGL((attn_combine_slots<S::D, SG, Slot>), dim3((unsigned)pairs, chunks),
                                dim3(kCombineThreads), 0, stream, a, m.seq_lens, m.q_start,
-                               m.unit_start, m.slot_o, m.slot_lse, m.out);
+                               m.unit_start, static_cast<const Slot*>(m.slot_o), m.slot_lse, m.out);
         };
         if (pairs <= 0) return;
         // more than one and a half rounds of slots per planned pair (the average; a
@@ -1991,8 +1993,8 @@ bool launch_persist(const PArgs& a, const MPtrs& m, const AttnPlan::Class& pl, i
         const std::integral_constant<int, 1> alone;
         const std::integral_constant<int, 4> shared;
         const bool share = 2 * (int64_t)a.nwg > 3 * kCombineSlots * pairs && wgs4 <= 8 * (int64_t)device_cus();
-        if (pl.slot_f32) share ? combine(shared, f32x4_t{}) : combine(alone, f32x4_t{});
-        else share ? combine(shared, uint2{}) : combine(alone, uint2{});
+        if (pl.slot_f32) share ? combine(shared, float{}) : combine(alone, float{});
+        else share ? combine(shared, uint16_t{}) : combine(alone, uint16_t{});
     });
 }
 
