@@ -1317,6 +1317,7 @@ void attn_combine_slots(
     if (rg >= rq.rg) return;
     const int ROWS = a.rows_per_group;
     const int group_rows = min(ROWS, a.group * rq.n - rg * ROWS);  // rows of this row group
+    if ((int)blockIdx.y * RPB >= group_rows) return;  // before the divisions of owner_of
     const bool empty = rq.nb == 0;
     int wf = 0, wl = 0;
     if (!empty) {
