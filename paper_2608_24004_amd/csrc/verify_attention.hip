@@ -43,7 +43,7 @@ struct AttnArgs {
     const int32_t* q_start;
     void* out;
     float* part_o;    // [total_q][Hq][max_splits][D] partial outputs, sums of 2^(score - m) v
-    float2* part_ml;  // [total_q][Hq][max_splits]    each split's maximum m and sum of 2^(score - m)
+    float* part_ml;   // [total_q][Hq][max_splits][2] each split's maximum m and sum of 2^(score - m)
     const float* sinks;  // [Hq] sink logits (natural-log units) or null
     const void* k_new;   // fused append: [total_q][Hkv][D] new keys and values, or null
     const void* v_new;
@@ -110,6 +110,7 @@ __device__ __forceinline__ SeqGeom seq_geom(const AttnArgs& a, int i) {
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 // callers' fp32 tensors and the workspace need only be aligned to a float
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2u_t __attribute__((ext_vector_type(2), aligned(4)));
 
 // Maximum of v over lanes l, l ^ 16, l ^ 32, l ^ 48 (the four lanes that hold
 // one row of an MFMA result tile).  Each permlane swap exchanges half of the
@@ -372,7 +373,8 @@ __global__ __launch_bounds__(kAttnThreads, f32_waves(D, RT)) void attn_f32(AttnA
                 *reinterpret_cast<f32x4u_t*>(dst + t * 16 + lg * 4) = den > 0.f ? O / div : f32x4_t{0.f, 0.f, 0.f, 0.f};
             }
             if (sg.nsplit > 1 && w == 0 && lg == 0)
-                a.part_ml[pi] = L > 0.f ? make_float2(M, L) : make_float2(-INFINITY, 0.f);
+                *reinterpret_cast<f32x2u_t*>(a.part_ml + 2 * pi) =
+                    L > 0.f ? f32x2u_t{M, L} : f32x2u_t{-INFINITY, 0.f};
         }
     }
 }
@@ -986,7 +988,7 @@ __attribute__((amdgpu_waves_per_eu(persist_waves_per_eu<TPW, NW>()))) void attn_
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
                     if constexpr (sizeof(Slot) == 4)
-                        *reinterpret_cast<f32x4_t*>(tb + dt * (kWave * 4)) = o[t][dt] * inv;
+                        *reinterpret_cast<f32x4u_t*>(tb + dt * (kWave * 4)) = o[t][dt] * inv;
                     else
                         *reinterpret_cast<uint2*>(tb + dt * (kWave * 4)) =
                             make_uint2(pack_bf16x2(o[t][dt][0] * inv, o[t][dt][1] * inv),
@@ -1301,7 +1303,7 @@ void attn_combine_slots(
     PArgs a, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_start,
     const int32_t* __restrict__ unit_start, const Slot* __restrict__ slot_o,
     const float* __restrict__ slot_lse, uint16_t* __restrict__ out) {
-    using Four = std::conditional_t<sizeof(Slot) == 2, uint2, f32x4_t>;  // four partial values
+    using Four = std::conditional_t<sizeof(Slot) == 2, uint2, f32x4u_t>;  // four partial values
     constexpr int QUADS = D / 4;                       // 4-dim vectors per row
     constexpr int RPB = kCombineThreads / QUADS / SG;  // rows per workgroup
     const int P = blockIdx.x;
@@ -1465,7 +1467,8 @@ __global__ __launch_bounds__(kAttnThreads) void attn_combine(AttnArgs a, int tot
     for (int base = 0; base < sg.nsplit; base += kWave) {
         const int64_t pi0 = item * a.max_splits + base;
         const int ns = min(kWave, sg.nsplit - base);
-        const float2 ml = lane < ns ? a.part_ml[pi0 + lane] : make_float2(-INFINITY, 0.f);
+        f32x2u_t ml = {-INFINITY, 0.f};
+        if (lane < ns) ml = *reinterpret_cast<const f32x2u_t*>(a.part_ml + 2 * (pi0 + lane));
         const float mnew = fmaxf(M, wave_max_xor(ml.x, kWave));
         if (mnew == -INFINITY) continue;
         // rescale what earlier splits summed (nothing yet: M = -inf gives 0)
@@ -1855,6 +1858,8 @@ int plan_class(const verify_attn_params* p, int32_t total_q, int64_t rows, int64
     const size_t values = (size_t)per * p->head_dim;
     c.cover_bytes = c.unit_bytes + align_up(std::max(most * values * sizeof(uint16_t), most_f32 * values * sizeof(float)), 256) +
                     align_up((size_t)std::max(most, most_f32) * per * sizeof(float), 256);
+    // (a launch of few, very long pairs is oversubscribed past most_f32)
+    c.cover_bytes = std::max(c.cover_bytes, c.unit_bytes + c.slot_o_bytes + c.slot_lse_bytes);
     return VERIFY_OK;
 }
 
@@ -1930,7 +1935,7 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
         if (pl.max_splits > 1) {
             const size_t items = (size_t)total_q * p->num_q_heads * pl.max_splits;
             pl.part_o_bytes = align_up(items * p->head_dim * sizeof(float), 256);
-            pl.part_ml_bytes = align_up(items * sizeof(float2), 256);
+            pl.part_ml_bytes = align_up(items * 2 * sizeof(float), 256);
         }
         pl.total_bytes = pl.part_o_bytes + pl.part_ml_bytes;
         pl.cover_bytes = pl.total_bytes;
@@ -1948,7 +1953,7 @@ int make_plan(const verify_attn_params* p, int32_t total_q, int32_t max_q_len,
             const size_t rows_splits = (size_t)std::max(most(kF32Items, 4), most(kF32MostItems * 33 / 32, kF32SplitBlocks));
             const size_t part = rows_splits * p->num_q_heads;
             pl.cover_bytes = std::max(pl.total_bytes, align_up(part * p->head_dim * sizeof(float), 256) +
-                                                          align_up(part * sizeof(float2), 256));
+                                                          align_up(part * 2 * sizeof(float), 256));
         }
     }
     *out = pl;
@@ -2123,7 +2128,7 @@ int attention_call(const verify_attn_params* params, int32_t total_q, int32_t ma
     a.out = out;
     a.part_o = pl.part_o_bytes ? static_cast<float*>(workspace) : nullptr;
     a.part_ml = pl.part_o_bytes
-                    ? reinterpret_cast<float2*>(static_cast<char*>(workspace) + pl.part_o_bytes)
+                    ? reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.part_o_bytes)
                     : nullptr;
     a.num_seqs = p.num_seqs;
     a.hq = p.num_q_heads;

@@ -510,3 +510,21 @@ def test_attention_workspace_covers_smaller_batches(dtype, kw, rows, tokens):
     sizes = [size(b, b * rows) for b in batches]
     assert sizes == sorted(sizes)
     assert all(size(b, b) <= n for b, n in zip(batches, sizes))
+
+
+@pytest.mark.parametrize("hkv", [1, 8])
+@pytest.mark.parametrize("blocks", [1, 16, 95, 1001, 8193, 300000, 1 << 24])
+@pytest.mark.parametrize("kw", [dict(), dict(head_dim=64), dict(sliding_window=4096)])
+def test_attention_workspace_query_covers_its_own_call(kw, blocks, hkv):
+    """The size that the query returns is enough for the call it was asked for
+    (a call without rows checks its workspace and launches nothing)."""
+    lib, dummy = av.library(), ctypes.c_void_p(0x1000)
+    for requests in (1, 3, 64):
+        p = _params(num_seqs=requests, num_kv_heads=hkv, num_q_heads=4 * hkv, max_blocks_per_seq=blocks, **kw)
+        rc, n = _ws(p, total_q=0, max_q=5, max_s=16 * blocks)
+        if rc == av.EUNSUPPORTED:
+            continue
+        assert rc == 0
+        for new in ((), (dummy, dummy)):
+            call = lib.verify_attention_append if new else lib.verify_attention
+            assert call(ctypes.byref(p), 0, 5, 16 * blocks, dummy, *new, *[dummy] * 5, None, dummy, dummy, n, None) == 0
